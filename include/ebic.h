@@ -61,8 +61,9 @@ enum { EBIC_ROW_MAJOR = 0, EBIC_COL_MAJOR = 1 };
  *           n_cols^2 * (wpad * 8 + 1) bytes of device memory (wpad =
  *           ceil(n_rows/64) rounded up to 16), plus a build scratch of
  *           ranks and bit-planes (about n_rows * n_cols * 3.7 bytes for up
- *           to 2048 columns) that the library keeps per device and reuses,
- *           and supports max_violations <= 3 (larger tolerances use DIRECT).
+ *           to 2048 columns) that the library keeps per device and reuses.
+ *           Tolerances max_violations of 4 to 63 are evaluated from the index
+ *           if it exists (they never build it), larger ones by DIRECT.
  *   AUTO:   INDEX when it fits the context's index budget, else DIRECT. */
 enum { EBIC_PATH_AUTO = 0, EBIC_PATH_DIRECT = 1, EBIC_PATH_INDEX = 2 };
 

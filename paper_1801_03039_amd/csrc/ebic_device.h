@@ -98,9 +98,8 @@ __device__ __forceinline__ void finish_part(int64_t c, uint32_t cnt, bool bad, i
 // in flight per lane, the same bytes).  The workgroup first stages the CBF
 // columns of the candidates it covers in LDS.  Per consecutive pair (p, q) a
 // lane reads lt(p,q) -- and lt(q,p) for the falling direction -- from the
-// pairwise order index and folds the violation words (complements) into K+1
-// saturating bit-sliced counters per direction: c[i] has bit b set when row
-// b has more than i violations.  lt(q,p) is read only for pairs that may
+// pairwise order index and folds the violation words (complements) into
+// bit-sliced counters per direction (Violations).  lt(q,p) is read only for pairs that may
 // tie (a set tie flag, or a set bit of the tie-pair bitmap); otherwise it is
 // ~lt(p,q) (lt(p,p) itself for a repeated column).  Single-run workgroups
 // look every staged pair up in the bitmap while staging, and run a loop
@@ -112,19 +111,60 @@ constexpr int kIdxLds = 4096;   // staged column entries per workgroup
 constexpr int kUnroll = 4;   // pairs per batch of loads (single-run default)
 constexpr int kWordsPerLane = 2;   // 64-row words per lane (flattened single-run tiling)
 
-template <int K, bool NEG>
-__device__ __forceinline__ void fold(uint64_t (&cu)[K + 1], uint64_t (&cd)[K + 1], uint64_t lt_pq,
-                                     uint64_t lt_qp) {
-    const uint64_t vu = ~lt_pq;
-#pragma unroll
-    for (int i = K; i > 0; --i) cu[i] |= cu[i - 1] & vu;
-    cu[0] |= vu;
-    if (NEG) {
-        const uint64_t vd = ~lt_qp;
-#pragma unroll
-        for (int i = K; i > 0; --i) cd[i] |= cd[i - 1] & vd;
-        cd[0] |= vd;
+// Violation counters of one 64-row word and direction, bit-sliced: bit b of
+// every word belongs to row b.  c[N - 1] holds the rejected rows, those with
+// more violations than the tolerance.
+//   K <= kIndexMaxViolations: the tolerance is K itself and the counters are
+//     saturating in unary (c[i]: more than i violations), K + 1 operations
+//     per pair and half-word.
+//   K = 2^BITS - 1 above: a binary counter of BITS bits for every tolerance
+//     k <= K.  It starts at K - k, so the (k + 1)-th violation carries out of
+//     its top bit, and the carry is kept in c[BITS]: 2 BITS + 1 operations,
+//     where the unary form would take k + 1 and as many registers.
+template <int K>
+struct Violations {
+    static constexpr bool kUnary = K <= kIndexMaxViolations;
+    static constexpr int bits() {
+        int b = 0;
+        while ((1 << b) - 1 < K) ++b;
+        return b;
     }
+    static constexpr int N = kUnary ? K + 1 : bits() + 1;
+    static_assert(kUnary || K == (1 << bits()) - 1, "binary counters hold 2^bits - 1");
+
+    __device__ __forceinline__ static void start(uint64_t (&c)[N], int32_t k) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) c[i] = 0ull;
+        if constexpr (!kUnary) {
+#pragma unroll
+            for (int i = 0; i < N - 1; ++i) c[i] = (((K - k) >> i) & 1) ? ~0ull : 0ull;
+        }
+    }
+    __device__ __forceinline__ static void add(uint64_t (&c)[N], uint64_t v) {
+        if constexpr (kUnary) {
+#pragma unroll
+            for (int i = K; i > 0; --i) c[i] |= c[i - 1] & v;
+            c[0] |= v;
+        } else {
+#pragma unroll
+            for (int i = 0; i < N - 1; ++i) {
+                const uint64_t carry = c[i] & v;
+                c[i] ^= v;
+                v = carry;
+            }
+            c[N - 1] |= v;
+        }
+    }
+};
+
+// One pair of one word: a violation of the rising trend is a row outside
+// lt(p,q), of the falling trend a row outside lt(q,p).
+template <int K, bool NEG>
+__device__ __forceinline__ void fold(uint64_t (&cu)[Violations<K>::N],
+                                     uint64_t (&cd)[Violations<K>::N], uint64_t lt_pq,
+                                     uint64_t lt_qp) {
+    Violations<K>::add(cu, ~lt_pq);
+    if (NEG) Violations<K>::add(cd, ~lt_qp);
 }
 
 // LDS of one tile: the staged CBF columns, for whole-candidate tiles the
@@ -295,11 +335,13 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
         valid[v] = (active && ok_range && w0 + v < W) ? tail_bits(n, w0 + v, W) : 0ull;
         any_valid |= valid[v];
     }
-    uint64_t cu[V][K + 1], cd[V][K + 1];
+    constexpr int NC = Violations<K>::N, OVER = NC - 1;   // counters, rejected rows
+    uint64_t cu[V][NC], cd[V][NC];
 #pragma unroll
-    for (int v = 0; v < V; ++v)
-#pragma unroll
-        for (int i = 0; i <= K; ++i) cu[v][i] = cd[v][i] = 0ull;
+    for (int v = 0; v < V; ++v) {
+        Violations<K>::start(cu[v], R.k);
+        Violations<K>::start(cd[v], R.k);
+    }
     bool bad = false;
 
     // Per-lane work, instantiated for columns in LDS or in global memory and
@@ -395,7 +437,7 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
                 uint64_t live = 0;
 #pragma unroll
                 for (int v = 0; v < V; ++v)
-                    live |= valid[v] & ~(NEG ? (cu[v][K] & cd[v][K]) : cu[v][K]);
+                    live |= valid[v] & ~(NEG ? (cu[v][OVER] & cd[v][OVER]) : cu[v][OVER]);
                 return live != 0ull;
             };
             // Whole batches of UU pairs, then the last L - t < UU pairs as one
@@ -471,7 +513,7 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
                 uint64_t live = 0;
 #pragma unroll
                 for (int v = 0; v < V; ++v)
-                    live |= valid[v] & ~(NEG ? (cu[v][K] & cd[v][K]) : cu[v][K]);
+                    live |= valid[v] & ~(NEG ? (cu[v][OVER] & cd[v][OVER]) : cu[v][OVER]);
                 if (live == 0ull) break;
             }
         }
@@ -500,8 +542,8 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
     int32_t rows = 0;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-        const uint64_t pos = valid[v] & ~cu[v][K];
-        const uint64_t neg = NEG ? (valid[v] & ~cd[v][K]) : 0ull;
+        const uint64_t pos = valid[v] & ~cu[v][OVER];
+        const uint64_t neg = NEG ? (valid[v] & ~cd[v][OVER]) : 0ull;
         rows += __popcll(pos | neg);
         if (masks && active && w0 + v < W) {
             masks[R.mask_base + ((int64_t)cl * 2 + 0) * W + w0 + v] = pos;

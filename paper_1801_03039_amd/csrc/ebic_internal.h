@@ -11,9 +11,13 @@
 
 namespace ebic {
 
-// Largest approximate tolerance the pairwise-index evaluator handles; it
-// keeps k+1 saturating bit-sliced violation counters per direction.
+// Tolerances of the pairwise-index evaluator.  Up to kIndexMaxViolations it
+// keeps k+1 saturating bit-sliced counters per direction (single-run and
+// batched kernels).  Single runs take tolerances up to
+// kIndexBinaryViolations from an index that already exists, with binary
+// counters.
 constexpr int kIndexMaxViolations = 3;
+constexpr int kIndexBinaryViolations = 63;
 
 // Candidate columns staged in LDS by the direct evaluator; longer series
 // read their tail from global memory.
@@ -87,7 +91,7 @@ struct IndexRun {
     int64_t cand_base;       // index of the run's first candidate in the launch
     int64_t mask_base;       // first mask word of the run (when masks are written)
     int32_t cpw;             // batched tiles: whole candidates per tile (0: flattened tiles)
-    int32_t reserved;
+    int32_t k;               // tolerance (read for k > kIndexMaxViolations)
     const uint32_t *tbits;   // tie-pair bitmap (single-run launches; batched runs read `tie`)
 };
 
@@ -197,6 +201,10 @@ bool pack_valid_cbf(ebic_ctx *ctx, const int32_t *offsets, const int32_t *cols, 
 
 hipError_t launch_eval_direct(const float *a, int64_t n, int64_t npad, int32_t m, int64_t W,
                               const EvalArgs &e, hipStream_t stream);
+
+// The launch of launch_eval_index for kIndexMaxViolations < e.k <=
+// kIndexBinaryViolations (ebic_tolerance.hip).
+void launch_eval_index_binary(const IndexRun &R, const EvalArgs &e, bool ties, hipStream_t stream);
 
 // `ties`: two distinct columns of the matrix have a tied or unordered row;
 // when false the falling test never reads the tie-pair bitmap or reverse

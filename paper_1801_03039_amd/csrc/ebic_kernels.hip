@@ -15,7 +15,7 @@
 //
 // One evaluation is one kernel launch: the part of each candidate that
 // finishes last writes its count and fitness.
-#include "ebic_device.h"
+#include "ebic_index_eval.h"
 
 namespace ebic {
 namespace {
@@ -318,18 +318,6 @@ __global__ __launch_bounds__(kBlock) void eval_direct_kernel(
     }
 }
 
-template <int K, bool NEG, int U, int V, bool ALIGNED, int TIES, bool OFF32, bool TAIL>
-__global__ __launch_bounds__(kAlignedThreads) void eval_index_kernel(
-    IndexRun R, uint32_t cpw, const int32_t *__restrict__ offsets,
-    const int32_t *__restrict__ cols, int64_t n_entries, int32_t sigma,
-    uint64_t *__restrict__ masks, unsigned long long *__restrict__ acc,
-    int32_t *__restrict__ counts, double *__restrict__ fitness) {
-    __shared__ TileLds lds;
-    index_tile<K, NEG, U, V, ALIGNED, TIES, OFF32, TAIL>(R, blockIdx.x, cpw, offsets, cols,
-                                                         n_entries, sigma, masks, acc, counts,
-                                                         fitness, lds);
-}
-
 }  // namespace
 
 // ----------------------------------------------------------- launchers --
@@ -386,67 +374,6 @@ hipError_t launch_eval_direct(const float *a, int64_t n, int64_t npad, int32_t m
     return hipGetLastError();
 }
 
-// Falling trends consult the tie-pair bitmap (and read reverse words) only
-// when two distinct columns of the matrix tie somewhere (`ties`); otherwise
-// lt(q,p) is ~lt(p,q) for every pair of distinct columns.  The bitmap is
-// staged in LDS, so a pair's test is an LDS read rather than a load of its
-// byte flag (measured 10.6 -> 9.6 us per launch for the expression
-// workload, whose matrix has 10 tied pairs).
-template <int K, int U, int V, bool ALIGNED, bool OFF32, bool TAIL>
-static void launch_index_o(const IndexRun &R, uint32_t cpw, dim3 grid, dim3 block,
-                           const EvalArgs &e, bool ties, hipStream_t stream) {
-    if (e.negative && ties)
-        hipLaunchKernelGGL((eval_index_kernel<K, true, U, V, ALIGNED, kTieBitmap, OFF32, TAIL>), grid, block,
-                           0, stream, R, cpw, e.offsets, e.cols, e.n_entries, e.sigma, e.masks,
-                           e.acc, e.counts, e.fitness);
-    else if (e.negative)
-        hipLaunchKernelGGL((eval_index_kernel<K, true, U, V, ALIGNED, kTieNone, OFF32, TAIL>), grid, block,
-                           0, stream, R, cpw, e.offsets, e.cols, e.n_entries, e.sigma, e.masks,
-                           e.acc, e.counts, e.fitness);
-    else
-        hipLaunchKernelGGL((eval_index_kernel<K, false, U, V, ALIGNED, kTieNone, OFF32, TAIL>), grid, block,
-                           0, stream, R, cpw, e.offsets, e.cols, e.n_entries, e.sigma, e.masks,
-                           e.acc, e.counts, e.fitness);
-}
-
-// 32-bit index offsets when the whole index is below 4 GiB.
-template <int K, int U, int V, bool ALIGNED, bool TAIL = false>
-static void launch_index_t(const IndexRun &R, uint32_t cpw, dim3 grid, dim3 block,
-                           const EvalArgs &e, bool ties, hipStream_t stream) {
-    const uint64_t bytes = (uint64_t)R.m * (uint64_t)R.m * (uint64_t)R.wpad * 8ull;
-    if (bytes <= 0xFFFFFFFFull)
-        launch_index_o<K, U, V, ALIGNED, true, TAIL>(R, cpw, grid, block, e, ties, stream);
-    else
-        launch_index_o<K, U, V, ALIGNED, false, TAIL>(R, cpw, grid, block, e, ties, stream);
-}
-
-// Whole-candidate workgroups.  With 4 words per lane, as many candidates as
-// fit in 256 lanes.  With 1 or 2, the candidate count (up to 320 lanes) that
-// leaves the fewest idle lanes in the workgroup's whole waves: e.g. 2
-// candidates of 157 lanes in 5 waves instead of 1 in 3 waves with 35 idle
-// lanes (measured 6% faster at 20000 rows, 7% at 5000; with 4 words per
-// lane the same rule was slower).
-template <int K, int U, int V, bool TAIL = false>
-static void launch_aligned(const IndexRun &R, const EvalArgs &e, bool ties, hipStream_t stream) {
-    const int64_t Wg = (R.W + V - 1) / V;
-    int64_t cpw = kBlock / Wg;
-    if (V <= 2) {
-        int64_t best = INT64_MAX;
-        for (int64_t c = 1; c <= kBlock && c * Wg <= kAlignedThreads; ++c) {
-            const int64_t th = (c * Wg + kWave - 1) / kWave * kWave;
-            const int64_t idle = (th - c * Wg) * 4096 / th;   // idle share, 1/4096 units
-            if (idle < best) {
-                best = idle;
-                cpw = c;
-            }
-        }
-    }
-    const int64_t threads = (cpw * Wg + kWave - 1) / kWave * kWave;
-    const dim3 grid((unsigned)((R.P + cpw - 1) / cpw));
-    launch_index_t<K, U, V, true, TAIL>(R, (uint32_t)cpw, grid, dim3((unsigned)threads), e,
-                                        ties, stream);
-}
-
 // Tiling by matrix height.  Up to 1024 words (65536 rows) a workgroup holds
 // whole candidates: 1 word per lane up to 128 words, 2 up to 320 (measured
 // faster than 1 from 128 words on: half the lanes, twice the loads in
@@ -483,13 +410,15 @@ static void launch_index_k(const IndexRun &R, const EvalArgs &e, bool ties, hipS
 hipError_t launch_eval_index(const uint64_t *idx, const uint32_t *tbits, bool ties, int64_t n,
                              int32_t m, int64_t W, int64_t wpad, const EvalArgs &e,
                              hipStream_t stream) {
-    const IndexRun R{idx, nullptr, e.logt, n, W, wpad, m, e.P, 0, 0, 0, 0, tbits};
+    const IndexRun R{idx, nullptr, e.logt, n, W, wpad, m, e.P, 0, 0, 0, e.k, tbits};
     switch (e.k) {
     case 0: launch_index_k<0, kUnroll>(R, e, ties, stream); break;
     case 1: launch_index_k<1, kUnroll>(R, e, ties, stream); break;
     case 2: launch_index_k<2, kUnroll>(R, e, ties, stream); break;
     case 3: launch_index_k<3, kUnroll>(R, e, ties, stream); break;
-    default: return hipErrorInvalidValue;
+    default:
+        if (e.k < 0 || e.k > kIndexBinaryViolations) return hipErrorInvalidValue;
+        launch_eval_index_binary(R, e, ties, stream);
     }
     return hipGetLastError();
 }

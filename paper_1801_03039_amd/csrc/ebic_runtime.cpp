@@ -198,12 +198,32 @@ bool params_ok(ebic_ctx *ctx, const ebic_params *p, ebic_status *st) {
     return true;
 }
 
+// Largest grid (in lanes) of one launch over P candidates: the index path
+// takes a lane per (candidate, word) at most, the direct path 8 workgroups
+// of 256 lanes per candidate.
+int64_t launch_lanes(const ebic_ctx *ctx, int32_t P, bool use_index) {
+    return use_index ? (int64_t)P * ctx->W : (int64_t)P * 8 * 256;
+}
+
+// Whether a tolerance above kIndexMaxViolations is evaluated from the order
+// index: only from one that exists (such a call never builds it under AUTO),
+// and only for populations that the direct kernel takes in one launch too,
+// so the same calls are accepted on both paths.
+bool binary_index(const ebic_ctx *ctx, const ebic_params *p, int32_t P) {
+    return ctx->idx_built && p->max_violations <= kIndexBinaryViolations &&
+           launch_lanes(ctx, P, true) <= kMaxLaunchThreads &&
+           launch_lanes(ctx, P, false) <= kMaxLaunchThreads;
+}
+
 // Decide the evaluator for this call; builds the index on first need.
-ebic_status choose_path(ebic_ctx *ctx, const ebic_params *p, bool *use_index) {
-    const bool k_ok = p->max_violations <= kIndexMaxViolations;
+ebic_status choose_path(ebic_ctx *ctx, const ebic_params *p, int32_t P, bool *use_index) {
     *use_index = false;
-    if (ctx->path == EBIC_PATH_DIRECT || !k_ok) return EBIC_OK;
+    if (ctx->path == EBIC_PATH_DIRECT) return EBIC_OK;
     if (ctx->path == EBIC_PATH_AUTO && ctx->idx_bytes > ctx->idx_budget) return EBIC_OK;
+    if (p->max_violations > kIndexMaxViolations) {
+        *use_index = binary_index(ctx, p, P);
+        return EBIC_OK;
+    }
     ebic_status st = build_index(ctx);
     if (st != EBIC_OK) {
         if (ctx->path == EBIC_PATH_INDEX) return st;
@@ -214,8 +234,7 @@ ebic_status choose_path(ebic_ctx *ctx, const ebic_params *p, bool *use_index) {
 }
 
 ebic_status launch_all(ebic_ctx *ctx, const EvalArgs &e, bool use_index, hipStream_t s) {
-    const int64_t items = use_index ? (int64_t)e.P * ctx->W : (int64_t)e.P * 8 * 256;
-    if (items > kMaxLaunchThreads)
+    if (launch_lanes(ctx, e.P, use_index) > kMaxLaunchThreads)
         return fail(ctx, EBIC_E_ARG, "population too large for one launch; split it");
     if (use_index)
         HIP_TRY(ctx, launch_eval_index(
@@ -367,12 +386,13 @@ ebic_status evaluate_device_impl(ebic_ctx *ctx, const int32_t *d_offsets, const 
         st = ensure_scratch(ctx, P);
         if (st != EBIC_OK) return st;
         acc = ctx->d_acc;
-        st = choose_path(ctx, params, &use_index);
+        st = choose_path(ctx, params, P, &use_index);
         if (st != EBIC_OK) return st;
     } else {
         use_index = ctx->idx_built && ctx->path != EBIC_PATH_DIRECT &&
-                    params->max_violations <= kIndexMaxViolations &&
                     !(ctx->path == EBIC_PATH_AUTO && ctx->idx_bytes > ctx->idx_budget);
+        if (params->max_violations > kIndexMaxViolations)
+            use_index = use_index && binary_index(ctx, params, P);
     }
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     EvalArgs e{d_offsets, d_cols, P, n_entries, params->sigma, params->max_violations,
@@ -494,7 +514,7 @@ ebic_status ebic_evaluate(ebic_ctx *ctx, const int32_t *offsets, const int32_t *
     if (mask_words && (st = grow(ctx, ctx->d_masks, ctx->cap_masks, mask_words, false)) != EBIC_OK)
         return st;
     bool use_index = false;
-    if ((st = choose_path(ctx, params, &use_index)) != EBIC_OK) return st;
+    if ((st = choose_path(ctx, params, P, &use_index)) != EBIC_OK) return st;
 
     hipStream_t s = ctx->stream;
     std::memcpy(ctx->h_cbf, offsets, sizeof(int32_t) * ((size_t)P + 1));
