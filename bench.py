@@ -177,7 +177,7 @@ def algorithmic_bytes(depth, n, P, sum_L, negative, want_masks, ties=None, any_t
 
 
 KERNEL_SOURCES = {
-    "eval_index_kernel": ("ebic_kernels.hip", "ebic_device.h"),
+    "eval_index_kernel": ("ebic_kernels.hip", "ebic_index_eval.h", "ebic_device.h"),
     "eval_index_batch_kernel": ("ebic_batch_kernels.hip", "ebic_device.h"),
 }
 

@@ -202,8 +202,8 @@ uint64_t fill_runs(ebic_batch *b, const Request &q, int32_t words, int32_t whole
         const int32_t P = via_index(b, q, r) ? q.P[(size_t)r] : 0;
         const uint64_t items = (uint64_t)((c->W + words - 1) / words);
         const int32_t k = cpw[(size_t)r];
-        b->h_runs[i] = IndexRun{c->d_idx, c->d_tie, c->d_log, c->n, c->W, c->wpad, c->m, P,
-                                cand[(size_t)r], maskw[(size_t)r], k, 0};
+        b->h_runs[i] = IndexRun{c->d_idx, c->d_tie, c->d_log, c->n, c->W, c->wpad, c->m, P, cand[(size_t)r],
+                                maskw[(size_t)r], k, q.params->max_violations, tie_bitmap(c)};
         b->h_tile_base[i] = (uint32_t)tiles;
         tiles += k ? ((uint64_t)P + k - 1) / k : ((uint64_t)P * items + 255) / 256;
     }
@@ -964,8 +964,8 @@ ebic_status ebic_batch_evolve_device(ebic_batch *b, const uint64_t *seeds, int32
         ebic_ctx *c = b->ctx[(size_t)r];
         const uint64_t items = (uint64_t)((c->W + words - 1) / words);
         const int32_t cpw = (whole && items <= 256) ? (int32_t)(256 / items) : 0;
-        iruns[(size_t)r] = IndexRun{c->d_idx, c->d_tie, c->d_log, c->n, c->W, c->wpad, c->m, P,
-                                    r * stride, 0, cpw, 0};
+        iruns[(size_t)r] = IndexRun{c->d_idx, c->d_tie, c->d_log, c->n, c->W, c->wpad, c->m, P, r * stride,
+                                    0, cpw, params->eval.max_violations, tie_bitmap(c)};
         tile_base[(size_t)r] = (uint32_t)tiles;
         tiles += cpw ? ((uint64_t)P + cpw - 1) / cpw : ((uint64_t)P * items + 255) / 256;
     }

@@ -130,7 +130,7 @@ static hipError_t launch_batch_uv(const BatchLaunch &b, hipStream_t stream) {
     switch (b.k) {
     case 0: launch_batch_k<0, U, V>(b, stream); break;
     case 1: launch_batch_k<1, U, V>(b, stream); break;
-    case 2: launch_batch_k<2, U, V>(b, stream); break;
+    case 2:
     case 3: launch_batch_k<3, U, V>(b, stream); break;
     default: return hipErrorInvalidValue;
     }

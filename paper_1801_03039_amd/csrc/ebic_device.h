@@ -97,91 +97,151 @@ __device__ __forceinline__ void finish_part(int64_t c, uint32_t cnt, bool bad, i
 // loop, and are read with 16-byte loads when V > 1 (fewer waves, more loads
 // in flight per lane, the same bytes).  The workgroup first stages the CBF
 // columns of the candidates it covers in LDS.  Per consecutive pair (p, q) a
-// lane reads lt(p,q) -- and lt(q,p) for the falling direction -- from the
-// pairwise order index and folds the violation words (complements) into
-// bit-sliced counters per direction (Violations).  lt(q,p) is read only for pairs that may
-// tie (a set tie flag, or a set bit of the tie-pair bitmap); otherwise it is
-// ~lt(p,q) (lt(p,p) itself for a repeated column).  Single-run workgroups
-// look every staged pair up in the bitmap while staging, and run a loop
-// without any tie test when none is set.  Loads for kUnroll pairs are issued
-// before any is consumed (the lane's latency chain is one order-word round
-// trip per kUnroll pairs), and a lane stops once every row of its word is
-// rejected in every enabled direction.
-constexpr int kIdxLds = 4096;   // staged column entries per workgroup
+// lane reads lt(p,q) from the pairwise order index and folds the violation
+// words into bit-sliced counters per direction (Violations).  A row that
+// does not rise falls, unless the pair ties on it: lt(q,p) is ~lt(p,q)
+// (lt(p,p) itself for a repeated column), and is read only for pairs that
+// may tie (a set bit of the tie-pair bitmap).
+//
+// Two loops.  The fast one serves workgroups whose columns all lie in the
+// matrix and whose pairs never tie, which staging finds out: there a pair
+// costs one LDS read (the byte or 128-byte offsets of its order row, formed
+// once per staged column), one address and 2 to 3 operations per half-word
+// and direction, and no column is checked.  The general one serves the rest
+// (tied pairs, malformed candidates, series past the staging area).  Loads
+// for U pairs are issued before any is consumed (the lane's latency chain is
+// one order-word round trip per U pairs), and a lane stops once every row of
+// its words is rejected in every enabled direction.
+constexpr int kPreLds = 2048;   // staged column entries per workgroup
 constexpr int kUnroll = 4;   // pairs per batch of loads (single-run default)
 constexpr int kWordsPerLane = 2;   // 64-row words per lane (flattened single-run tiling)
 
-// Violation counters of one 64-row word and direction, bit-sliced: bit b of
-// every word belongs to row b.  c[N - 1] holds the rejected rows, those with
-// more violations than the tolerance.
-//   K <= kIndexMaxViolations: the tolerance is K itself and the counters are
-//     saturating in unary (c[i]: more than i violations), K + 1 operations
-//     per pair and half-word.
-//   K = 2^BITS - 1 above: a binary counter of BITS bits for every tolerance
-//     k <= K.  It starts at K - k, so the (k + 1)-th violation carries out of
-//     its top bit, and the carry is kept in c[BITS]: 2 BITS + 1 operations,
-//     where the unary form would take k + 1 and as many registers.
+// Any bitwise function of three words in one operation (v_bitop3_b32): T is
+// its truth table, written as the same expression over kA, kB and kC.
+constexpr uint32_t kA = 0xF0, kB = 0xCC, kC = 0xAA;
+template <uint32_t T>
+__device__ __forceinline__ uint32_t bitop3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, T & 0xFF);
+}
+
+// Violation counters of one 32-row half-word and direction, bit-sliced: bit
+// b of every word belongs to row b.  For a class K = 2^BITS - 1 of
+// tolerances k <= K the counter has BITS bits and starts at K - k, so the
+// (k + 1)-th violation carries out of its top bit; c[OVER] collects the
+// carries, the rows with more than k violations.
+//
+// The violations of four pairs are first added up: from the words o of "the
+// row rises on this pair", r = t0 + 2 t1 + 4 t2 rising pairs (two half and
+// one full adder, 6 operations) are the falling direction's violations, and
+// 4 - r the rising one's (2 more), so the adder is shared by the directions
+// and a pair costs 3.3 operations per half-word for k = 1 in both
+// directions, 5.5 for k = 7; counted pair by pair in unary, with the
+// complements formed separately, it was about 9 and 25.
 template <int K>
 struct Violations {
-    static constexpr bool kUnary = K <= kIndexMaxViolations;
     static constexpr int bits() {
         int b = 0;
         while ((1 << b) - 1 < K) ++b;
         return b;
     }
-    static constexpr int N = kUnary ? K + 1 : bits() + 1;
-    static_assert(kUnary || K == (1 << bits()) - 1, "binary counters hold 2^bits - 1");
+    static constexpr int BITS = bits(), OVER = BITS, N = BITS + 1;
+    static_assert(K == (1 << BITS) - 1, "tolerance classes are 2^bits - 1");
+    uint32_t c[N];
 
-    __device__ __forceinline__ static void start(uint64_t (&c)[N], int32_t k) {
+    __device__ __forceinline__ void start(int32_t k) {
 #pragma unroll
-        for (int i = 0; i < N; ++i) c[i] = 0ull;
-        if constexpr (!kUnary) {
-#pragma unroll
-            for (int i = 0; i < N - 1; ++i) c[i] = (((K - k) >> i) & 1) ? ~0ull : 0ull;
-        }
+        for (int i = 0; i < BITS; ++i) c[i] = (((K - k) >> i) & 1) ? ~0u : 0u;
+        c[OVER] = 0u;
     }
-    __device__ __forceinline__ static void add(uint64_t (&c)[N], uint64_t v) {
-        if constexpr (kUnary) {
+    // one violation on the rows of v
+    __device__ __forceinline__ void add(uint32_t v) {
 #pragma unroll
-            for (int i = K; i > 0; --i) c[i] |= c[i - 1] & v;
-            c[0] |= v;
-        } else {
-#pragma unroll
-            for (int i = 0; i < N - 1; ++i) {
-                const uint64_t carry = c[i] & v;
-                c[i] ^= v;
-                v = carry;
-            }
-            c[N - 1] |= v;
+        for (int i = 0; i < BITS; ++i) {
+            const uint32_t carry = c[i] & v;
+            c[i] ^= v;
+            v = carry;
         }
+        c[OVER] |= v;
+    }
+    // n0 + 2 n1 + 4 n2 violations
+    __device__ __forceinline__ void add(uint32_t n0, uint32_t n1, uint32_t n2) {
+        uint32_t carry = 0u;
+        auto digit = [&](auto bit, uint32_t d) {
+            constexpr int i = decltype(bit)::value;
+            if constexpr (i < BITS) {
+                const uint32_t x = c[i];
+                if constexpr (i == 0) {
+                    c[i] = x ^ d;
+                    carry = x & d;
+                } else {
+                    c[i] = bitop3<kA ^ kB ^ kC>(x, d, carry);
+                    carry = bitop3<(kA & kB) | (kA & kC) | (kB & kC)>(x, d, carry);
+                }
+            } else {
+                c[OVER] |= d;
+            }
+        };
+        digit(std::integral_constant<int, 0>{}, n0);
+        digit(std::integral_constant<int, 1>{}, n1);
+        digit(std::integral_constant<int, 2>{}, n2);
+#pragma unroll
+        for (int i = 3; i < BITS; ++i) {
+            const uint32_t x = c[i];
+            c[i] = x ^ carry;
+            carry &= x;
+        }
+        c[OVER] |= carry;
     }
 };
 
-// One pair of one word: a violation of the rising trend is a row outside
-// lt(p,q), of the falling trend a row outside lt(q,p).
+// Folds four pairs of one half-word into both directions' counters.
 template <int K, bool NEG>
-__device__ __forceinline__ void fold(uint64_t (&cu)[Violations<K>::N],
-                                     uint64_t (&cd)[Violations<K>::N], uint64_t lt_pq,
-                                     uint64_t lt_qp) {
-    Violations<K>::add(cu, ~lt_pq);
-    if (NEG) Violations<K>::add(cd, ~lt_qp);
+__device__ __forceinline__ void fold4(Violations<K> &up, Violations<K> &down, uint32_t o0,
+                                      uint32_t o1, uint32_t o2, uint32_t o3) {
+    if constexpr (K == 0) {
+        up.c[0] = bitop3<kA | ~(kB & kC)>(up.c[0], bitop3<kA & kB & kC>(o0, o1, o2), o3);
+        if constexpr (NEG)
+            down.c[0] = bitop3<kA | kB | kC>(down.c[0], bitop3<kA | kB | kC>(o0, o1, o2), o3);
+        return;
+    }
+    const uint32_t s = bitop3<kA ^ kB ^ kC>(o0, o1, o2);
+    const uint32_t c = bitop3<(kA & kB) | (kA & kC) | (kB & kC)>(o0, o1, o2);
+    const uint32_t t0 = s ^ o3, c1 = s & o3, t1 = c ^ c1, t2 = c & c1;
+    // 4 - r: its digits are t0, t0 ^ t1 and "no pair rises"
+    if constexpr (K == 1) {
+        // both upper digits overflow: r <= 2
+        up.c[1] |= bitop3<~(kA | (kB & kC))>(t2, t1, t0);
+        up.add(t0);
+    } else {
+        up.add(t0, t0 ^ t1, bitop3<~(kA | kB | kC)>(t0, t1, t2));
+    }
+    if constexpr (NEG) down.add(t0, t1, t2);
 }
 
+// A staged column x: the order row of pair (p, q) starts at
+// row(p) + col(q), row = x m S and col = x S for a row stride S.  With a
+// 32-bit index (OFF32) S is in bytes, otherwise in units of 128 bytes (rows
+// are multiples of 128 bytes).
+struct PreCol {
+    uint32_t row, col;
+};
+
 // LDS of one tile: the staged CBF columns, for whole-candidate tiles the
-// per-candidate row counts and malformed flags, and the tie-pair bitmap.
+// per-candidate row counts and malformed flags, the tie-pair bitmap, and
+// what staging found.
 struct TileLds {
-    int32_t cols[kIdxLds];
+    PreCol pre[kPreLds];
     int32_t rows[kBlock];
     int32_t bad[kBlock];
     uint32_t tbits[kTieWords];
-    int32_t any_tied;        // a staged consecutive pair is in the tie-pair bitmap
+    uint64_t tied[kPreLds / 64];   // bit e % 64 of word e / 64: staged column e may
+                                   // tie with the one before it, or repeats it
+    uint32_t found;                // what staging found (kFound*)
+    uint32_t n_tied;               // bits set in `tied`
 };
-
-// How the falling test learns that a pair has a tied row (lt(q,p) is then
-// read from the index instead of taken as ~lt(p,q)): never (the matrix has
-// no tied pair), from the m*m byte flags (one load per pair), or from the
-// tie-pair bitmap staged in LDS.
-enum TieMode { kTieNone = 0, kTieFlags = 1, kTieBitmap = 2 };
+constexpr uint32_t kFoundBad = 1;    // a staged column is out of range, or a lane's
+                                     // series lies outside the staged span
+constexpr uint32_t kFoundTied = 2;   // a staged pair may tie
 
 // V consecutive order words of one pair, read with 16-byte loads when V > 1
 // (the caller keeps the address 16-byte aligned).
@@ -231,8 +291,7 @@ struct ShortBatch<0> {
 //     kAlignedThreads lanes); counts are summed with LDS atomics and the
 //     first lane of each candidate writes its result after a workgroup
 //     barrier -- no global atomics and no accumulator scratch.
-template <int K, bool NEG, int U, int V, bool ALIGNED, int TIES = kTieFlags, bool OFF32 = false,
-          bool TAIL = false>
+template <int K, bool NEG, int U, int V, bool ALIGNED, bool OFF32 = false, bool TAIL = false>
 __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uint32_t cpw,
                                            const int32_t *__restrict__ offsets,
                                            const int32_t *__restrict__ cols, int64_t n_entries,
@@ -242,9 +301,7 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
                                            double *__restrict__ fitness, TileLds &lds) {
     // (V <= 8 keeps a wave's per-candidate row count within 16 bits below)
     static_assert(V == 1 || V == 2 || V == 4 || V == 8, "words per lane");
-    int32_t *const s_cols = lds.cols;
     const auto idx = as_global(R.idx);
-    const auto tie = as_global(R.tie);
     const auto logt = as_global(R.logt);
     const int64_t n = R.n, W = R.W, wpad = R.wpad;
     const int32_t m = R.m, P = R.P;
@@ -272,11 +329,14 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
     const int64_t w0 = (int64_t)g * V;                           // first word of the item
     const int64_t c = R.cand_base + cl;                          // candidate in the launch
 
-    // the tie-pair bitmap, ordered before its first use by the barrier below
-    if constexpr (NEG && TIES == kTieBitmap) {
+    // The tie-pair bitmap (null: no two distinct columns tie) in LDS; the
+    // byte flag of a pair whose bit is set says whether it ties.
+    const bool ties = NEG && R.tbits != nullptr;
+    if (NEG && ties) {
         const auto tb = as_global(R.tbits);
         for (int i = tid; i < kTieWords; i += (int)blockDim.x) lds.tbits[i] = tb[i];
     }
+    if (tid == 0) lds.found = lds.n_tied = 0;
     auto in_bitmap = [&](int64_t pq) -> bool {
         const uint32_t h = tie_hash((uint32_t)pq);
         return ((lds.tbits[h >> 5] >> (h & 31)) & 1u) != 0;
@@ -286,10 +346,10 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
     const bool ok_range = start >= 0 && end <= n_entries && end > start;
     const int32_t L = ok_range ? (int32_t)(end - start) : 0;
 
-    // Stage the columns of candidates [c_lo, c_hi] in LDS when they fit and
-    // every lane's series lies inside the staged span (always, for a
-    // well-formed CBF); otherwise the whole workgroup reads them from global
-    // memory.  The choice is uniform over the workgroup.
+    // Stage the columns of candidates [c_lo, c_hi] in LDS when they fit.
+    // They are used when every lane's series lies inside the staged span
+    // (always, for a well-formed CBF); otherwise the whole workgroup reads
+    // them from global memory.  Every choice is uniform over the workgroup.
     const int64_t b0 = offsets[R.cand_base + c_lo], b1 = offsets[R.cand_base + c_hi + 1];
     int32_t *const s_rows = lds.rows;
     int32_t *const s_bad = lds.bad;
@@ -297,35 +357,46 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
         s_rows[tid] = 0;
         s_bad[tid] = 0;
     }
-    if (tid == 0) lds.any_tied = 0;
-    const bool span_ok = b0 >= 0 && b1 <= n_entries && b1 >= b0 && b1 - b0 <= kIdxLds;
-    const bool lane_ok = !ok_range || (start >= b0 && end <= b1);
-    const bool use_lds = __syncthreads_and(span_ok && lane_ok) != 0;
-    // Staging also checks every staged column: when none is out of range
-    // (the common case) the per-candidate validation below is skipped.  With
-    // the tie-pair bitmap it also looks up every staged consecutive pair
-    // (pairs that straddle two candidates included): a workgroup none of
-    // whose pairs is in the bitmap runs the tie-free loop.
-    bool staged_bad = true;
-    [[maybe_unused]] bool staged_tie = true;
-    if (use_lds) {
-        bool inval = false, any_tied = false;
-        for (int32_t e = tid; e < (int32_t)(b1 - b0); e += (int32_t)blockDim.x) {
-            const int32_t x = cols[b0 + e];
-            inval |= x < 0 || x >= m;
-            s_cols[e] = x;
-            if constexpr (NEG && TIES == kTieBitmap) {
-                if (e > 0) {
-                    const int32_t xp = cols[b0 + e - 1];
-                    if (x >= 0 && x < m && xp >= 0 && xp < m && x != xp)
-                        any_tied |= in_bitmap((int64_t)xp * m + x);
-                }
-            }
+    // row strides of the staged offsets; the unit form has to fit 32 bits
+    const uint32_t col_s = OFF32 ? (uint32_t)wpad * 8u : (uint32_t)(wpad / 16);
+    const uint32_t row_s = (uint32_t)m * col_s;
+    const bool staged = b0 >= 0 && b1 <= n_entries && b1 >= b0 && b1 - b0 <= kPreLds &&
+                        (OFF32 || (uint64_t)m * (uint64_t)m * (uint64_t)(wpad / 16) < (1ull << 32));
+    const int32_t span = staged ? (int32_t)(b1 - b0) : 0;
+    __syncthreads();   // lds.found is cleared, the bitmap is in LDS
+    bool wrong = staged && ok_range && (start < b0 || end > b1);
+    uint32_t n_tied = 0;
+    for (int32_t e = tid; (e & ~63) < span; e += (int32_t)blockDim.x) {   // whole waves
+        const bool in_span = e < span;
+        const int32_t x = in_span ? cols[b0 + e] : 0;
+        int32_t xp = -1;
+        if constexpr (NEG) xp = in_span && e > 0 ? cols[b0 + e - 1] : -1;
+        const bool in = x >= 0 && x < m;
+        wrong |= in_span && !in;
+        if (in_span) lds.pre[e] = PreCol{(uint32_t)x * row_s, (uint32_t)x * col_s};
+        // pairs that straddle two candidates included (no series reads them)
+        if constexpr (NEG) {
+            const bool pair = in_span && in && xp >= 0 && xp < m;
+            const int64_t pq = (int64_t)xp * m + x;
+            const uint64_t t = ballot(
+                pair && (x == xp || (ties && in_bitmap(pq) && as_global(R.tie)[pq] != 0)));
+            n_tied += (uint32_t)__popcll(t);
+            if (lane == 0) lds.tied[e >> 6] = t;
         }
-        if (any_tied) lds.any_tied = 1;
-        staged_bad = __syncthreads_or(inval) != 0;
-        staged_tie = lds.any_tied != 0;
     }
+    {
+        const uint32_t f = (ballot(wrong) != 0ull ? kFoundBad : 0u) |
+                           (n_tied != 0u ? kFoundTied : 0u);
+        if (f != 0u && lane == 0) {
+            atomicOr(&lds.found, f);
+            if (NEG) atomicAdd(&lds.n_tied, n_tied);
+        }
+    }
+    __syncthreads();
+    const uint32_t found = __builtin_amdgcn_readfirstlane(lds.found);
+    const bool good = staged && (found & kFoundBad) == 0;
+    const bool many_ties = NEG && (found & kFoundTied) != 0 &&
+                           __builtin_amdgcn_readfirstlane(lds.n_tied) * 4u > (uint32_t)span;
     const int32_t lds0 = (int32_t)(start - b0);
 
     uint64_t valid[V];
@@ -335,215 +406,235 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
         valid[v] = (active && ok_range && w0 + v < W) ? tail_bits(n, w0 + v, W) : 0ull;
         any_valid |= valid[v];
     }
-    constexpr int NC = Violations<K>::N, OVER = NC - 1;   // counters, rejected rows
-    uint64_t cu[V][NC], cd[V][NC];
+    constexpr int OVER = Violations<K>::OVER;
+    uint64_t up[V], down[V];   // rows of each word rejected in each direction
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-        Violations<K>::start(cu[v], R.k);
-        Violations<K>::start(cd[v], R.k);
-    }
-    bool bad = false;
+    for (int v = 0; v < V; ++v) up[v] = down[v] = ~0ull;
+    auto half = [](uint64_t x, int h) -> uint32_t { return (uint32_t)(h ? x >> 32 : x); };
+    // The lane of a candidate's first word reports whether it is malformed.
+    bool bad = active && g == 0 && !ok_range;
 
-    // Per-lane work, instantiated for columns in LDS or in global memory and
-    // for a tie mode (TIES, or kTieNone for a workgroup without tied pairs).
-    auto lane_work = [&](auto from_lds, auto tie_mode, auto unroll) {
-        constexpr bool kLds = decltype(from_lds)::value;
-        constexpr int TM = decltype(tie_mode)::value;
-        constexpr int UU = decltype(unroll)::value;
-        auto tied = [&](int64_t pq) -> uint8_t {
-            if constexpr (TM == kTieFlags) return tie[pq];
-            if constexpr (TM == kTieBitmap) return in_bitmap(pq) ? 1 : 0;
-            return 0;
-        };
-        auto col = [&](int32_t t) -> int32_t {
-            if constexpr (kLds) return s_cols[lds0 + t];
-            else return cols[start + t];
-        };
-        // The lane of the first word validates every column (batched,
-        // branch-free reads; skipped when staging found every staged column
-        // in range) and reports the outcome with its part; other lanes only
-        // clamp column indices so that no read leaves the index.
-        if (active && g == 0) bad = !ok_range;
-        if (active && g == 0 && (!kLds || staged_bad)) {
-            for (int32_t t = 0; t < L; t += UU) {
-                int32_t x[UU];
+    if (good && !many_ties) {
+        if (any_valid) {
+            const PreCol *const pre = lds.pre + lds0;
+            constexpr bool REST_FIRST = K > 1;
+            Violations<K> cu[V][2], cd[V][2];   // rising, falling; low and high half-word
 #pragma unroll
-                for (int u = 0; u < UU; ++u) x[u] = col(min(t + u, L - 1));
+            for (int v = 0; v < V; ++v)
 #pragma unroll
-                for (int u = 0; u < UU; ++u) bad |= (x[u] < 0 || x[u] >= m);
-            }
-        }
-        if (!any_valid) return;
-        // Address of the words of pair row `pq`: with OFF32 (index < 4 GiB)
-        // a 32-bit byte offset from the uniform base, which the compiler
-        // forms as a scalar base plus one offset register per load.
-        auto words_at = [&](int64_t pq) {
-            if constexpr (OFF32) {
-                typedef const __attribute__((address_space(1))) char *gchar;
-                const uint32_t off = ((uint32_t)pq * (uint32_t)wpad + (uint32_t)w0) * 8u;
-                return (global_ptr<uint64_t>)((gchar)idx + off);
-            } else {
-                return idx + w0 + pq * wpad;
-            }
-        };
-        if constexpr (TAIL) {
-            int32_t p = col(0);
-            p = (p < 0 || p >= m) ? 0 : p;
-            // One batch of N consecutive pairs from pair t (t + N <= L): the
-            // column reads and order-word loads are all issued before any is
-            // consumed.  Returns whether a row of the lane's words is still
-            // undecided.
-            auto batch = [&](auto n, int32_t t) -> bool {
-                constexpr int N = decltype(n)::value;
-                int32_t q[N];
-#pragma unroll
-                for (int u = 0; u < N; ++u) {
-                    const int32_t x = col(t + u);
-                    q[u] = (x < 0 || x >= m) ? 0 : x;
+                for (int h = 0; h < 2; ++h) {
+                    cu[v][h].start(R.k);
+                    cd[v][h].start(R.k);
                 }
-                uint64_t lu[N][V], ld[N][V];
-                uint8_t tf[N];
-                int32_t pp = p;
-#pragma unroll
-                for (int u = 0; u < N; ++u) {
-                    const int64_t pq = (int64_t)pp * m + q[u];
-                    load_words<V>(words_at(pq), lu[u]);
-                    if (NEG) tf[u] = tied(pq);
-                    pp = q[u];
-                }
-                if (NEG) {
-                    // lt(q,p) is the complement of lt(p,q) unless the pair ties
-                    pp = p;
-#pragma unroll
-                    for (int u = 0; u < N; ++u) {
-                        if (TM != kTieNone && tf[u]) {
-                            load_words<V>(words_at((int64_t)q[u] * m + pp), ld[u]);
-                        } else {
-                            // a repeated column is its own reverse: lt(p,p) = 0
-                            // (the byte flags mark it as tied instead)
-                            const bool self = TM != kTieFlags && q[u] == pp;
-#pragma unroll
-                            for (int v = 0; v < V; ++v) ld[u][v] = self ? lu[u][v] : ~lu[u][v];
-                        }
-                        pp = q[u];
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < N; ++u)
-#pragma unroll
-                    for (int v = 0; v < V; ++v)
-                        fold<K, NEG>(cu[v], cd[v], lu[u][v], NEG ? ld[u][v] : 0ull);
-                p = q[N - 1];
+            auto over = [&](const Violations<K> (&c)[V][2], int v) -> uint64_t {
+                return ((uint64_t)c[v][1].c[OVER] << 32) | c[v][0].c[OVER];
+            };
+            // whether a row of the lane's words is still accepted in some direction
+            auto undecided = [&]() -> bool {
                 uint64_t live = 0;
 #pragma unroll
                 for (int v = 0; v < V; ++v)
-                    live |= valid[v] & ~(NEG ? (cu[v][OVER] & cd[v][OVER]) : cu[v][OVER]);
+                    live |= valid[v] & ~(NEG ? (over(cu, v) & over(cd, v)) : over(cu, v));
                 return live != 0ull;
             };
-            // Whole batches of UU pairs, then the last L - t < UU pairs as one
-            // shorter batch: no load reads past the end of the series.
-            int32_t t = 1;
-            bool undecided = true;
-            for (; t + UU <= L; t += UU)
-                if (!(undecided = batch(std::integral_constant<int, UU>{}, t))) break;
-            if (undecided)
-                ShortBatch<UU - 1>::run(L - t, [&](auto n) { (void)batch(n, t); });
-        } else {
-            const int32_t last = L - 1;
-            int32_t p = col(0);
-            p = (p < 0 || p >= m) ? 0 : p;
-            for (int32_t t = 1; t < L; t += UU) {
-                // Column reads and order-word loads of the batch are issued
-                // unconditionally (slots past the end repeat the last pair, a
-                // harmless in-bounds read whose words are then ignored).
-                int32_t q[UU];
+            typedef const __attribute__((address_space(1))) char *gchar;
+            const auto words = OFF32 ? (gchar)idx : (gchar)(idx + w0);
+            const uint32_t w_off = OFF32 ? (uint32_t)w0 * 8u : 0u;
+            // The order words of N pairs, pair i(u) in slot u: the offset
+            // reads and loads are all issued before any word is consumed.
+            uint64_t lt[U][V];
+            auto load_row = [&](uint32_t off, uint64_t (&o)[V]) {
+                if constexpr (OFF32)
+                    load_words<V>((global_ptr<uint64_t>)(words + (off + w_off)), o);
+                else
+                    load_words<V>((global_ptr<uint64_t>)(words + ((uint64_t)off << 7)), o);
+            };
+            auto load = [&](auto n_pairs, auto &&i) {
 #pragma unroll
-                for (int u = 0; u < UU; ++u) {
-                    const int32_t x = col(min(t + u, last));
-                    q[u] = (x < 0 || x >= m) ? 0 : x;
-                }
-                uint64_t lu[UU][V], ld[UU][V];
-                uint8_t tf[UU];
-                int32_t pp = p;
-                int64_t pq_prev = 0;
-#pragma unroll
-                for (int u = 0; u < UU; ++u) {
-                    // a slot past the end re-reads the words of the last
-                    // pair (just fetched) rather than a diagonal row
-                    int64_t pq = (int64_t)pp * m + q[u];
-                    if (u > 0) pq = t + u < L ? pq : pq_prev;
-                    pq_prev = pq;
-                    load_words<V>(words_at(pq), lu[u]);
-                    if (NEG) tf[u] = tied(pq);
-                    pp = q[u];
-                }
-#pragma unroll
-                for (int u = 0; u < UU; ++u) {
-                    const bool in = t + u < L;
-#pragma unroll
-                    for (int v = 0; v < V; ++v) lu[u][v] = in ? lu[u][v] : ~0ull;
-                    if (NEG) tf[u] = in ? tf[u] : 0;
-                }
-                if (NEG) {
-                    // lt(q,p) is the complement of lt(p,q) unless the pair ties;
-                    // slots past the end of the series break nothing.
-                    pp = p;
-#pragma unroll
-                    for (int u = 0; u < UU; ++u) {
-                        if (TM != kTieNone && tf[u]) {
-                            load_words<V>(words_at((int64_t)q[u] * m + pp), ld[u]);
-                        } else {
-                            // a repeated column is its own reverse: lt(p,p) = 0
-                            // (the byte flags mark it as tied instead)
-                            const bool self = TM != kTieFlags && q[u] == pp;
-#pragma unroll
-                            for (int v = 0; v < V; ++v) ld[u][v] = self ? lu[u][v] : ~lu[u][v];
-                        }
-#pragma unroll
-                        for (int v = 0; v < V; ++v) ld[u][v] = t + u < L ? ld[u][v] : ~0ull;
-                        pp = q[u];
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < UU; ++u)
-#pragma unroll
-                    for (int v = 0; v < V; ++v)
-                        fold<K, NEG>(cu[v], cd[v], lu[u][v], NEG ? ld[u][v] : 0ull);
-                p = pp;
-                uint64_t live = 0;
+                for (int u = 0; u < decltype(n_pairs)::value; ++u)
+                    load_row(pre[i(u) - 1].row + pre[i(u)].col, lt[u]);
+            };
+            // slot u's pair, on the rows of `in`
+            auto fold1 = [&](int u, uint32_t in) {
 #pragma unroll
                 for (int v = 0; v < V; ++v)
-                    live |= valid[v] & ~(NEG ? (cu[v][OVER] & cd[v][OVER]) : cu[v][OVER]);
-                if (live == 0ull) break;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const uint32_t o = half(lt[u][v], h);
+                        cu[v][h].add(~o & in);
+                        if (NEG) cd[v][h].add(o & in);
+                    }
+            };
+            // The (L - 1) mod U pairs that do not fill a batch, from pair t.
+            const int32_t rest = (L - 1) & (U - 1);
+            auto short_batch = [&](int32_t t) {
+                if constexpr (TAIL) {
+                    // as one shorter batch
+                    ShortBatch<U - 1>::run(rest, [&](auto r) {
+                        load(r, [&](int u) { return t + u; });
+#pragma unroll
+                        for (int u = 0; u < decltype(r)::value; ++u) fold1(u, ~0u);
+                    });
+                } else if (U > 1 && rest > 0) {
+                    // as a batch whose surplus slots repeat the last pair and
+                    // break nothing
+                    load(std::integral_constant<int, U - 1>{},
+                         [&](int u) { return t + min(u, rest - 1); });
+#pragma unroll
+                    for (int u = 0; u < U - 1; ++u) fold1(u, u < rest ? ~0u : 0u);
+                }
+            };
+            // The loop below takes a row that does not rise for a falling one.
+            // Tied rows (in neither order row; every row of a repeated
+            // column) break the falling trend too, and are counted here from
+            // both order rows of the pairs that may tie, two at a time.
+            if (NEG && (found & kFoundTied) != 0) {
+                const int32_t e0 = lds0 + 1, e1 = lds0 + L;   // pairs end in staged columns [e0, e1)
+                for (int32_t wi = e0 >> 6; wi < (e1 + 63) >> 6; ++wi) {
+                    uint64_t bits = lds.tied[wi];
+                    if (wi == e0 >> 6) bits &= ~0ull << (e0 & 63);
+                    if (wi == e1 >> 6) bits &= ~(~0ull << (e1 & 63));
+                    while (bits != 0ull) {
+                        int32_t e[2];
+                        bool have[2];
+                        uint64_t o[2][2][V];
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) {
+                            have[u] = bits != 0ull;
+                            e[u] = have[u] ? wi * 64 + __builtin_ctzll(bits) : e0;
+                            bits &= bits - 1;
+                            load_row(lds.pre[e[u] - 1].row + lds.pre[e[u]].col, o[u][0]);
+                            load_row(lds.pre[e[u]].row + lds.pre[e[u] - 1].col, o[u][1]);
+                        }
+#pragma unroll
+                        for (int u = 0; u < 2; ++u)
+#pragma unroll
+                            for (int v = 0; v < V; ++v)
+#pragma unroll
+                                for (int h = 0; h < 2; ++h)
+                                    cd[v][h].add(have[u] ? ~(half(o[u][0][v], h) |
+                                                             half(o[u][1][v], h)) : 0u);
+                    }
+                }
+            }
+            if constexpr (REST_FIRST) short_batch(1);
+            int32_t t = REST_FIRST ? 1 + rest : 1;
+            bool more = true;
+            if (t + U <= L) do {
+                load(std::integral_constant<int, U>{}, [&](int u) { return t + u; });
+                constexpr int N4 = U / 4 * 4;   // pairs folded four at a time
+#pragma unroll
+                for (int u = 0; u < N4; u += 4)
+#pragma unroll
+                    for (int v = 0; v < V; ++v)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+                            fold4<K, NEG>(cu[v][h], cd[v][h], half(lt[u][v], h),
+                                          half(lt[u + 1][v], h), half(lt[u + 2][v], h),
+                                          half(lt[u + 3][v], h));
+#pragma unroll
+                for (int u = N4; u < U; ++u) fold1(u, ~0u);
+                t += U;
+                more = undecided();
+            } while (t + U <= L && more);
+            if constexpr (!REST_FIRST)
+                if (more) short_batch(t);
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                up[v] = over(cu, v);
+                if (NEG) down[v] = over(cd, v);
             }
         }
-    };
-    using tie_none = std::integral_constant<int, kTieNone>;
-    using tie_mode = std::integral_constant<int, TIES>;
-    using unroll = std::integral_constant<int, U>;
-    if constexpr (NEG && TIES == kTieBitmap) {
-        // Workgroups with a tied pair (rare) take batches of at most 2
-        // pairs: the reverse words then never hold the kernel's register
-        // count above that of the tie-free loop.
-        using unroll_tied = std::integral_constant<int, (U < 2 ? U : 2)>;
-        if (use_lds && !staged_bad && !staged_tie)
-            lane_work(std::true_type{}, tie_none{}, unroll{});
-        else if (use_lds)
-            lane_work(std::true_type{}, tie_mode{}, unroll_tied{});
-        else
-            lane_work(std::false_type{}, tie_mode{}, unroll_tied{});
     } else {
-        if (use_lds)
-            lane_work(std::true_type{}, tie_mode{}, unroll{});
-        else
-            lane_work(std::false_type{}, tie_mode{}, unroll{});
+        // Both order rows of every pair, each direction from its own, at most
+        // four words at a time so that this loop needs no more registers than
+        // the fast one.  pair_at(t, rising): offset (in words) of the order
+        // row of the series' pair that ends at position t, or its reverse's.
+        constexpr int VV = V < 4 ? V : 4, UU = U < 4 / VV ? U : 4 / VV;
+        auto by_words = [&](auto &&pair_at) {
+#pragma clang loop unroll(disable)
+            for (int v0 = 0; v0 < V; v0 += VV) {
+                uint64_t rows_v[VV];
+#pragma unroll
+                for (int v = 0; v < VV; ++v)
+                    rows_v[v] = (active && ok_range && w0 + v0 + v < W)
+                                    ? tail_bits(n, w0 + v0 + v, W) : 0ull;
+                if (rows_v[0] == 0ull) break;   // no words past the last one
+                Violations<K> cu[VV][2], cd[VV][2];
+#pragma unroll
+                for (int v = 0; v < VV; ++v)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        cu[v][h].start(R.k);
+                        cd[v][h].start(R.k);
+                    }
+                auto over = [](const Violations<K> (&c)[2]) -> uint64_t {
+                    return ((uint64_t)c[1].c[OVER] << 32) | c[0].c[OVER];
+                };
+                const auto words = idx + w0 + v0;
+                bool more = true;
+                for (int32_t t = 1; t < L && more; t += UU) {
+                    uint64_t lu[UU][VV], ld[UU][VV];
+#pragma unroll
+                    for (int u = 0; u < UU; ++u) {   // surplus slots repeat the last pair
+                        const int32_t i = min(t + u, L - 1);
+                        load_words<VV>(words + pair_at(i, true), lu[u]);
+                        if (NEG) load_words<VV>(words + pair_at(i, false), ld[u]);
+                    }
+#pragma unroll
+                    for (int u = 0; u < UU; ++u) {
+                        const uint32_t in = t + u < L ? ~0u : 0u;
+#pragma unroll
+                        for (int v = 0; v < VV; ++v)
+#pragma unroll
+                            for (int h = 0; h < 2; ++h) {
+                                cu[v][h].add(~half(lu[u][v], h) & in);
+                                if (NEG) cd[v][h].add(~half(ld[u][v], h) & in);
+                            }
+                    }
+                    uint64_t live = 0;
+#pragma unroll
+                    for (int v = 0; v < VV; ++v)
+                        live |= rows_v[v] & ~(NEG ? (over(cu[v]) & over(cd[v])) : over(cu[v]));
+                    more = live != 0ull;
+                }
+#pragma unroll
+                for (int x = 0; x < V; ++x)
+                    if (x / VV * VV == v0) {
+                        up[x] = over(cu[x % VV]);
+                        if (NEG) down[x] = over(cd[x % VV]);
+                    }
+            }
+        };
+        if (good) {
+            constexpr int64_t unit = OFF32 ? 1 : 128;   // offsets in bytes or 128 bytes
+            by_words([&](int32_t t, bool rising) -> int64_t {
+                const PreCol p = lds.pre[lds0 + t - 1], q = lds.pre[lds0 + t];
+                return (int64_t)(rising ? p.row + q.col : q.row + p.col) * unit / 8;
+            });
+        } else {
+            // columns from global memory, clamped so that no read leaves the
+            // index; the lane of the candidate's first word checks them all
+            if (active && g == 0)
+                for (int32_t t = 0; t < L; ++t) {
+                    const int32_t x = cols[start + t];
+                    bad |= x < 0 || x >= m;
+                }
+            auto col = [&](int32_t t) -> int64_t {
+                const int32_t x = cols[start + t];
+                return x < 0 || x >= m ? 0 : x;
+            };
+            by_words([&](int32_t t, bool rising) -> int64_t {
+                return (rising ? col(t - 1) * m + col(t) : col(t) * m + col(t - 1)) * wpad;
+            });
+        }
     }
 
     int32_t rows = 0;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-        const uint64_t pos = valid[v] & ~cu[v][OVER];
-        const uint64_t neg = NEG ? (valid[v] & ~cd[v][OVER]) : 0ull;
+        const uint64_t pos = valid[v] & ~up[v];
+        const uint64_t neg = NEG ? (valid[v] & ~down[v]) : 0ull;
         rows += __popcll(pos | neg);
         if (masks && active && w0 + v < W) {
             masks[R.mask_base + ((int64_t)cl * 2 + 0) * W + w0 + v] = pos;

@@ -11,13 +11,11 @@
 
 namespace ebic {
 
-// Tolerances of the pairwise-index evaluator.  Up to kIndexMaxViolations it
-// keeps k+1 saturating bit-sliced counters per direction (single-run and
-// batched kernels).  Single runs take tolerances up to
-// kIndexBinaryViolations from an index that already exists, with binary
-// counters.
+// Tolerances of the pairwise-index evaluator: up to kIndexMaxViolations in
+// single-run and batched kernels; single runs take those up to
+// kIndexWideViolations from an index that already exists.
 constexpr int kIndexMaxViolations = 3;
-constexpr int kIndexBinaryViolations = 63;
+constexpr int kIndexWideViolations = 63;
 
 // Candidate columns staged in LDS by the direct evaluator; longer series
 // read their tail from global memory.
@@ -36,8 +34,8 @@ hipError_t launch_ingest(const float *src, int64_t n, int32_t m, int64_t ld, int
 // Tie-pair filter of the falling test: a bitmap of kTieBits bits in which
 // ordered pair id p*m + q (p != q) sets bit tie_hash(p*m + q) when columns
 // p and q have a tied or unordered row.  Every tied pair sets its bit, so a
-// clear bit proves lt(q,p) = ~lt(p,q) on the valid rows; a set bit of an
-// untied pair (a hash collision) only costs a read of the true reverse word.
+// clear bit proves lt(q,p) = ~lt(p,q) on the valid rows; only a set bit is
+// followed by a read of the pair's byte flag.
 constexpr int kTieBitsLog2 = 13;
 constexpr int kTieWords = (1 << kTieBitsLog2) / 32;   // 1 KiB
 __host__ __device__ inline uint32_t tie_hash(uint32_t pq) {
@@ -91,8 +89,8 @@ struct IndexRun {
     int64_t cand_base;       // index of the run's first candidate in the launch
     int64_t mask_base;       // first mask word of the run (when masks are written)
     int32_t cpw;             // batched tiles: whole candidates per tile (0: flattened tiles)
-    int32_t k;               // tolerance (read for k > kIndexMaxViolations)
-    const uint32_t *tbits;   // tie-pair bitmap (single-run launches; batched runs read `tie`)
+    int32_t k;               // tolerance
+    const uint32_t *tbits;   // tie-pair bitmap (nullptr: no two distinct columns tie)
 };
 
 // Batched launch shapes: unroll x words per lane is at most this.
@@ -203,15 +201,18 @@ hipError_t launch_eval_direct(const float *a, int64_t n, int64_t npad, int32_t m
                               const EvalArgs &e, hipStream_t stream);
 
 // The launch of launch_eval_index for kIndexMaxViolations < e.k <=
-// kIndexBinaryViolations (ebic_tolerance.hip).
-void launch_eval_index_binary(const IndexRun &R, const EvalArgs &e, bool ties, hipStream_t stream);
+// kIndexWideViolations (ebic_tolerance.hip).
+void launch_eval_index_wide(const IndexRun &R, const EvalArgs &e, hipStream_t stream);
 
-// `ties`: two distinct columns of the matrix have a tied or unordered row;
-// when false the falling test never reads the tie-pair bitmap or reverse
-// words.
-hipError_t launch_eval_index(const uint64_t *idx, const uint32_t *tbits, bool ties, int64_t n,
-                             int32_t m, int64_t W, int64_t wpad, const EvalArgs &e,
+// tbits: the tie-pair bitmap, or nullptr when no two distinct columns of the
+// matrix have a tied or unordered row (the falling test then reads no
+// reverse words).
+hipError_t launch_eval_index(const uint64_t *idx, const uint8_t *tie, const uint32_t *tbits,
+                             int64_t n, int32_t m, int64_t W, int64_t wpad, const EvalArgs &e,
                              hipStream_t stream);
+
+// The tie-pair bitmap of a context's built index (nullptr as above).
+const uint32_t *tie_bitmap(const ebic_ctx *ctx);
 
 }  // namespace ebic
 

@@ -375,50 +375,48 @@ hipError_t launch_eval_direct(const float *a, int64_t n, int64_t npad, int32_t m
 }
 
 // Tiling by matrix height.  Up to 1024 words (65536 rows) a workgroup holds
-// whole candidates: 1 word per lane up to 128 words, 2 up to 320 (measured
-// faster than 1 from 128 words on: half the lanes, twice the loads in
-// flight), 4 with 2 pairs per batch of loads up to 1024 (measured 7-13%
-// faster than 2 words from 391 to 1016 words, equal at 344); as many
-// candidates per workgroup as fit, and a workgroup just large enough (whole
-// waves) to hold them.  Taller matrices use the flattened tiling with 2
-// words per lane.  With 2 words per lane up to 256 words, the last batch of
-// each series is cut to its remaining pairs (no loads past the series end:
-// 8.25 -> 7.53 us at 10000 rows, 9.33 -> 8.51 at 15000); above 256 words the
-// extra registers of that form cost resident waves and it is slower (10.8
-// -> 14.1 us at 20000 rows).
+// whole candidates: 1 word per lane up to 128 words, 2 up to 320 (half the
+// lanes and twice the loads in flight: 9.2 against 11.5 us from 1 word at
+// 15000 rows), 4 up to 1024; taller matrices use the flattened tiling with 2
+// words per lane.  With 4 words, tolerances up to 1 take 2 pairs per batch
+// of loads (30000 rows, both directions, k = 1: 12.9 us, 13.8 with 4 pairs),
+// larger ones 4 pairs and a shorter last batch, whose shared adders save
+// more than their registers cost (k = 2: 15.0 us, 19.2 with 2 pairs).  8
+// pairs per batch with 1 or 2 words are slower (20000 rows, k = 1: 13.6
+// against 10.2 us).
 constexpr int64_t kTwoWordsMax = 320;
-constexpr int64_t kTailMax = 256;
 
-template <int K, int U>
-static void launch_index_k(const IndexRun &R, const EvalArgs &e, bool ties, hipStream_t stream) {
+template <int K>
+static void launch_index_k(const IndexRun &R, const EvalArgs &e, hipStream_t stream) {
     if (R.W <= kBlock / 2)
-        launch_aligned<K, U, 1>(R, e, ties, stream);
-    else if (R.W <= kTailMax)
-        launch_aligned<K, U, 2, true>(R, e, ties, stream);
+        launch_aligned<K, kUnroll, 1>(R, e, stream);
     else if (R.W <= kTwoWordsMax)
-        launch_aligned<K, U, 2>(R, e, ties, stream);
-    else if (R.W <= 4 * kBlock)
-        launch_aligned<K, 2, 4>(R, e, ties, stream);
-    else {
+        launch_aligned<K, kUnroll, 2>(R, e, stream);
+    else if (R.W <= 4 * kBlock) {
+        if constexpr (K <= 1)
+            launch_aligned<K, 2, 4>(R, e, stream);
+        else
+            launch_aligned<K, 4, 4, true>(R, e, stream);
+    } else {
         constexpr int V = kWordsPerLane;
         const int64_t total = (int64_t)R.P * ((R.W + V - 1) / V);
         const dim3 grid((unsigned)((total + kBlock - 1) / kBlock));
-        launch_index_t<K, U, V, false>(R, 0, grid, dim3(kBlock), e, ties, stream);
+        launch_index_t<K, kUnroll, V, false>(R, 0, grid, dim3(kBlock), e, stream);
     }
 }
 
-hipError_t launch_eval_index(const uint64_t *idx, const uint32_t *tbits, bool ties, int64_t n,
-                             int32_t m, int64_t W, int64_t wpad, const EvalArgs &e,
+hipError_t launch_eval_index(const uint64_t *idx, const uint8_t *tie, const uint32_t *tbits,
+                             int64_t n, int32_t m, int64_t W, int64_t wpad, const EvalArgs &e,
                              hipStream_t stream) {
-    const IndexRun R{idx, nullptr, e.logt, n, W, wpad, m, e.P, 0, 0, 0, e.k, tbits};
+    const IndexRun R{idx, tie, e.logt, n, W, wpad, m, e.P, 0, 0, 0, e.k, tbits};
     switch (e.k) {
-    case 0: launch_index_k<0, kUnroll>(R, e, ties, stream); break;
-    case 1: launch_index_k<1, kUnroll>(R, e, ties, stream); break;
-    case 2: launch_index_k<2, kUnroll>(R, e, ties, stream); break;
-    case 3: launch_index_k<3, kUnroll>(R, e, ties, stream); break;
+    case 0: launch_index_k<0>(R, e, stream); break;
+    case 1: launch_index_k<1>(R, e, stream); break;
+    case 2:
+    case 3: launch_index_k<3>(R, e, stream); break;
     default:
-        if (e.k < 0 || e.k > kIndexBinaryViolations) return hipErrorInvalidValue;
-        launch_eval_index_binary(R, e, ties, stream);
+        if (e.k < 0 || e.k > kIndexWideViolations) return hipErrorInvalidValue;
+        launch_eval_index_wide(R, e, stream);
     }
     return hipGetLastError();
 }

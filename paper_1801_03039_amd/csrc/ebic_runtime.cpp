@@ -209,8 +209,8 @@ int64_t launch_lanes(const ebic_ctx *ctx, int32_t P, bool use_index) {
 // index: only from one that exists (such a call never builds it under AUTO),
 // and only for populations that the direct kernel takes in one launch too,
 // so the same calls are accepted on both paths.
-bool binary_index(const ebic_ctx *ctx, const ebic_params *p, int32_t P) {
-    return ctx->idx_built && p->max_violations <= kIndexBinaryViolations &&
+bool wide_index(const ebic_ctx *ctx, const ebic_params *p, int32_t P) {
+    return ctx->idx_built && p->max_violations <= kIndexWideViolations &&
            launch_lanes(ctx, P, true) <= kMaxLaunchThreads &&
            launch_lanes(ctx, P, false) <= kMaxLaunchThreads;
 }
@@ -221,7 +221,7 @@ ebic_status choose_path(ebic_ctx *ctx, const ebic_params *p, int32_t P, bool *us
     if (ctx->path == EBIC_PATH_DIRECT) return EBIC_OK;
     if (ctx->path == EBIC_PATH_AUTO && ctx->idx_bytes > ctx->idx_budget) return EBIC_OK;
     if (p->max_violations > kIndexMaxViolations) {
-        *use_index = binary_index(ctx, p, P);
+        *use_index = wide_index(ctx, p, P);
         return EBIC_OK;
     }
     ebic_status st = build_index(ctx);
@@ -238,9 +238,8 @@ ebic_status launch_all(ebic_ctx *ctx, const EvalArgs &e, bool use_index, hipStre
         return fail(ctx, EBIC_E_ARG, "population too large for one launch; split it");
     if (use_index)
         HIP_TRY(ctx, launch_eval_index(
-                         ctx->d_idx,
-                         reinterpret_cast<const uint32_t *>(ctx->d_tie + tie_bits_offset(ctx->m)),
-                         ctx->any_tie, ctx->n, ctx->m, ctx->W, ctx->wpad, e, s));
+                         ctx->d_idx, ctx->d_tie, tie_bitmap(ctx), ctx->n, ctx->m, ctx->W,
+                         ctx->wpad, e, s));
     else
         HIP_TRY(ctx, launch_eval_direct(ctx->d_a, ctx->n, ctx->npad, ctx->m, ctx->W, e, s));
     return EBIC_OK;
@@ -392,7 +391,7 @@ ebic_status evaluate_device_impl(ebic_ctx *ctx, const int32_t *d_offsets, const 
         use_index = ctx->idx_built && ctx->path != EBIC_PATH_DIRECT &&
                     !(ctx->path == EBIC_PATH_AUTO && ctx->idx_bytes > ctx->idx_budget);
         if (params->max_violations > kIndexMaxViolations)
-            use_index = use_index && binary_index(ctx, params, P);
+            use_index = use_index && wide_index(ctx, params, P);
     }
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     EvalArgs e{d_offsets, d_cols, P, n_entries, params->sigma, params->max_violations,
@@ -407,6 +406,10 @@ ebic_status fail_status(ebic_ctx *ctx, ebic_status st, const char *msg) {
 
 void set_thread_error(const char *msg) { g_tls_error = msg; }
 ebic_status ensure_index(ebic_ctx *ctx) { return build_index(ctx); }
+const uint32_t *tie_bitmap(const ebic_ctx *ctx) {
+    if (!ctx->d_tie || !ctx->any_tie) return nullptr;
+    return reinterpret_cast<const uint32_t *>(ctx->d_tie + tie_bits_offset(ctx->m));
+}
 bool valid_cbf(ebic_ctx *ctx, const int32_t *offsets, const int32_t *cols, int32_t P,
                ebic_status *st) {
     return check_cbf(ctx, offsets, cols, P, st);
