@@ -1080,11 +1080,14 @@ def _mask_shape(masks, n_rows: int):
     return int(K), int(planes)
 
 
+_ROWS_GUESS = 1 << 20
+
+
 def mask_rows(masks, n_rows: int, capacity: Optional[int] = None, stream=None):
     """Row indices of each bicluster (``ebic_mask_rows``) from device masks
     [K][W] or [K][planes][W] (planes united).  Returns device tensors
     (offsets int64 [K+1], rows int32 [capacity]); with capacity None the
-    offsets are read back first and rows is sized to hold every list."""
+    offsets are read back and rows holds every list."""
     import torch as _t
     if not masks.is_cuda or not masks.is_contiguous():
         raise ValueError("masks must be a contiguous device tensor")
@@ -1093,18 +1096,26 @@ def mask_rows(masks, n_rows: int, capacity: Optional[int] = None, stream=None):
     if stream is None:
         stream = _t.cuda.current_stream(dev)
     offsets = _t.empty(K + 1, dtype=_t.int64, device=dev)
-    size_first = capacity is None
-    cap = 0 if size_first else int(capacity)
+    # Without a capacity the lists are written at once into room for
+    # _ROWS_GUESS entries (or every row of every bicluster, if that is less);
+    # only longer ones are written in a second call of their exact size.
+    cap = min(K * int(n_rows), _ROWS_GUESS) if capacity is None else int(capacity)
     rows = _t.empty(max(cap, 1), dtype=_t.int32, device=dev)
     args = [_vp(masks.data_ptr()), K, planes, int(n_rows), _vp(offsets.data_ptr()),
             _vp(rows.data_ptr()), cap, _vp(stream.cuda_stream)]
     _check(_mask_rows(*args))
-    if size_first:
-        stream.synchronize()
-        cap = int(offsets[-1].item())
-        rows = _t.empty(max(cap, 1), dtype=_t.int32, device=dev)
-        args[5], args[6] = _vp(rows.data_ptr()), cap
-        _check(_mask_rows(*args))
+    if capacity is None:
+        own = stream == _t.cuda.current_stream(dev)
+        if not own:
+            stream.synchronize()
+        total = int(offsets[-1].item())
+        if total > cap:
+            rows = _t.empty(total, dtype=_t.int32, device=dev)
+            args[5], args[6] = _vp(rows.data_ptr()), total
+            _check(_mask_rows(*args))
+        elif total < cap // 4 and own:   # leave no large buffer behind a short list
+            rows = rows[:total].clone()
+        cap = total
     return offsets, rows[:cap]
 
 

@@ -10,6 +10,7 @@
 
 #include <cstdint>
 #include <string>
+#include <type_traits>
 
 #include "ebic_internal.h"
 
@@ -22,11 +23,24 @@ __device__ inline uint64_t tail_word(uint64_t v, int64_t w, int64_t W, uint64_t 
     return w == W - 1 ? v & tail : v;
 }
 
-// Union of a bicluster's mask planes for word w.
+// Union of a bicluster's mask planes for word w.  PL: the number of planes
+// (1: one mask, 2: both trend directions) if the kernel is built for it, so
+// that their loads are in flight together; 0: `planes` at run time.
+template <int PL>
 __device__ inline uint64_t plane_or(const uint64_t *m, int32_t planes, int64_t W, int64_t w) {
-    uint64_t v = 0;
-    for (int32_t p = 0; p < planes; ++p) v |= m[(int64_t)p * W + w];
+    uint64_t v = m[w];
+    if constexpr (PL == 2) v |= m[W + w];
+    if constexpr (PL == 0)
+        for (int32_t p = 1; p < planes; ++p) v |= m[(int64_t)p * W + w];
     return v;
+}
+
+// f(integral_constant<int, PL>) for the plane count's kernel form.
+template <class F>
+void for_planes(int32_t planes, F &&f) {
+    if (planes == 1) f(std::integral_constant<int, 1>{});
+    else if (planes == 2) f(std::integral_constant<int, 2>{});
+    else f(std::integral_constant<int, 0>{});
 }
 
 template <typename T>
@@ -59,6 +73,7 @@ __device__ inline T block_exclusive_scan(T v, T *s_wave, T *total) {
 }
 
 // offsets[k + 1] = number of rows in bicluster k.  One block per bicluster.
+template <int PL>
 __global__ __launch_bounds__(kBlock) void mask_count_kernel(const uint64_t *masks, int32_t planes,
                                                             int64_t W, uint64_t tail,
                                                             int64_t *offsets) {
@@ -66,7 +81,7 @@ __global__ __launch_bounds__(kBlock) void mask_count_kernel(const uint64_t *mask
     const uint64_t *m = masks + k * planes * W;
     int64_t c = 0;
     for (int64_t w = threadIdx.x; w < W; w += kBlock)
-        c += __popcll(tail_word(plane_or(m, planes, W, w), w, W, tail));
+        c += __popcll(tail_word(plane_or<PL>(m, planes, W, w), w, W, tail));
     c = wave_sum(c);
     __shared__ int64_t s[kWaves];
     if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = c;
@@ -94,25 +109,66 @@ __global__ __launch_bounds__(kBlock) void offsets_scan_kernel(int64_t *offsets, 
 }
 
 // Row indices of bicluster k at rows[offsets[k] ...], increasing; entries at
-// or beyond `capacity` are not written.  One block per bicluster.
+// or beyond `capacity` are not written.  Block (k, s) writes the rows of the
+// s-th chunk of `chunk` words; where they start follows from the popcounts
+// of the words before, which the block reads again (16 chunks at most, so
+// the masks are read 8 times on average, from L2).  A wave takes 16 words
+// at a time: each word is made uniform, lane b holds its bit b, and the
+// set lanes store neighbouring entries.  Bound by latency at a search's
+// sizes: 100 lists from 20000 rows took 16.3 us with one block per
+// bicluster and a thread per word, storing its bits one after the other,
+// and take 5.2 us.
+constexpr int64_t kScatterWords = 16 * kWaves;   // words per block and step
+constexpr int64_t kScatterChunks = 16;           // blocks per bicluster at most
+template <int PL>
 __global__ __launch_bounds__(kBlock) void mask_scatter_kernel(const uint64_t *masks, int32_t planes,
                                                               int64_t W, uint64_t tail,
                                                               const int64_t *offsets, int32_t *rows,
-                                                              int64_t capacity) {
+                                                              int64_t capacity, int64_t chunk) {
     const int64_t k = blockIdx.x;
     const uint64_t *m = masks + k * planes * W;
-    __shared__ int64_t s_wave[kWaves];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t w_lo = (int64_t)blockIdx.y * chunk, w_hi = w_lo + chunk < W ? w_lo + chunk : W;
+    __shared__ int64_t s_part[kWaves];
+    __shared__ int32_t s_step[2][kWaves];
+    int64_t before = 0;
+    for (int64_t w = threadIdx.x; w < w_lo; w += kBlock)
+        before += __popcll(plane_or<PL>(m, planes, W, w));
+    before = wave_sum(before);
+    if (lane == 0) s_part[wv] = before;
+    __syncthreads();
     int64_t pos0 = offsets[k];
-    for (int64_t base = 0; base < W; base += kBlock) {
-        const int64_t w = base + threadIdx.x;
-        uint64_t v = w < W ? tail_word(plane_or(m, planes, W, w), w, W, tail) : 0;
-        int64_t total;
-        int64_t pos = pos0 + block_exclusive_scan((int64_t)__popcll(v), s_wave, &total);
-        while (v) {
-            const int b = __builtin_ctzll(v);
-            if (pos < capacity) rows[pos] = (int32_t)(w * 64 + b);
-            ++pos;
-            v &= v - 1;
+    for (int i = 0; i < kWaves; ++i) pos0 += s_part[i];
+    int step = 0;
+    for (int64_t w0 = w_lo; w0 < w_hi; w0 += kScatterWords, step ^= 1) {
+        // lanes 0..15: the wave's 16 words and their exclusive prefix sums
+        const int64_t w = w0 + 16 * wv + lane;
+        const uint64_t v =
+            lane < 16 && w < w_hi ? tail_word(plane_or<PL>(m, planes, W, w), w, W, tail) : 0ull;
+        const int32_t c = __popcll(v);
+        int32_t x = c;
+        for (int d = 1; d < 16; d <<= 1) {
+            const int32_t y = __shfl_up(x, d, 16);
+            if ((lane & 15) >= d) x += y;
+        }
+        if (lane == 15) s_step[step][wv] = x;
+        __syncthreads();   // (two sets: a wave may be one step ahead)
+        int32_t base = 0, total = 0;
+        for (int i = 0; i < kWaves; ++i) {
+            const int32_t t = s_step[step][i];
+            if (i < wv) base += t;
+            total += t;
+        }
+        const int32_t first = base + x - c;
+        for (int i = 0; i < 16; ++i) {
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, i);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), i);
+            const int32_t at = __builtin_amdgcn_readlane(first, i);
+            const uint64_t word = ((uint64_t)hi << 32) | lo;
+            const int64_t pos =
+                pos0 + at + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+            if (((word >> lane) & 1ull) && pos < capacity)
+                rows[pos] = (int32_t)((w0 + 16 * wv + i) * 64 + lane);
         }
         pos0 += total;
     }
@@ -125,90 +181,229 @@ struct SetView {
     const int32_t *cols;
 };
 
-// Number of distinct columns of list a[0..la) and how many of them occur in
-// b[0..lb), summed over the wave.
-__device__ inline void column_counts(const int32_t *a, int32_t la, const int32_t *b, int32_t lb,
-                                     int64_t *distinct, int64_t *shared) {
+// Whether the wave's lane value c occurs in list[0..n) before place `upto`.
+// The entries are read once per wave, 64 at a time, and made uniform: every
+// lane has to take part.
+__device__ inline bool occurs(const int32_t *list, int32_t n, int32_t c, int32_t upto) {
     const int lane = threadIdx.x & 63;
-    int64_t d = 0, s = 0;
-    for (int32_t i = lane; i < la; i += 64) {
-        const int32_t c = a[i];
-        bool first = true;
-        for (int32_t j = 0; j < i; ++j) first = first && a[j] != c;
-        if (!first) continue;
-        ++d;
-        bool in = false;
-        for (int32_t j = 0; j < lb; ++j) in = in || b[j] == c;
-        s += in ? 1 : 0;
+    bool in = false;
+    for (int32_t base = 0; base < n; base += 64) {
+        const int32_t cnt = n - base < 64 ? n - base : 64;
+        const int32_t x = base + lane < n ? list[base + lane] : 0;
+        for (int32_t j = 0; j < cnt; ++j) {
+            const int32_t entry = __builtin_amdgcn_readlane(x, j);
+            in |= base + j < upto && entry == c;
+        }
     }
-    *distinct = wave_sum(d);
-    *shared = wave_sum(s);
+    return in;
 }
 
-// J[f * E + e] for every pair; one wave per pair.
+// Distinct columns of the list a[0..la) (each counted at its first place)
+// and how many of them occur in b[0..lb), for lists of any length; the
+// results are uniform over the wave.
+__device__ inline void column_counts(const int32_t *a, int32_t la, const int32_t *b, int32_t lb,
+                                     int32_t *distinct, int32_t *shared) {
+    const int lane = threadIdx.x & 63;
+    int32_t d = 0, s = 0;
+    for (int32_t base = 0; base < la; base += 64) {
+        const int32_t i = base + lane;
+        const int32_t c = i < la ? a[i] : 0;
+        const int32_t end = base + 64 < la ? base + 64 : la;
+        const bool before = occurs(a, end, c, i);
+        const bool in = occurs(b, lb, c, lb);
+        const bool first = i < la && !before;
+        d += __popcll(__ballot(first));
+        s += __popcll(__ballot(first && in));
+    }
+    *distinct = d;
+    *shared = s;
+}
+
+// J[f * E + e] for every pair; a wave takes one found bicluster and TE
+// expected ones, whose words meet the found one's in registers (TE = 4 reads
+// 6 words for 4 pairs of 2-plane and 1-plane masks, TE = 1 3 for one).
+// The row counts are exact in T (32 bits up to INT32_MAX rows).  Bound by
+// latency at a search's sizes: 100 x 20 biclusters of 20000 rows took 16.2
+// us, most of it in column scans that waited for one entry after the other,
+// and take 8.3 us.
+template <typename T, int TE, int FP, int EP>
 __global__ __launch_bounds__(kBlock) void jaccard_kernel(SetView fs, int32_t F, SetView es,
                                                          int32_t E, int64_t W, uint64_t tail,
                                                          double *J) {
-    const int64_t pair = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
-    if (pair >= (int64_t)F * E) return;     // whole waves leave; no block barrier follows
-    const int32_t f = (int32_t)(pair / E), e = (int32_t)(pair % E);
-    const uint64_t *a = fs.masks + (int64_t)f * fs.planes * W;
-    const uint64_t *b = es.masks + (int64_t)e * es.planes * W;
+    const int32_t groups = (E + TE - 1) / TE;
+    const int64_t item = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
+    if (item >= (int64_t)F * groups) return;   // whole waves leave; no block barrier follows
+    const int32_t f = (int32_t)(item / groups), e0 = (int32_t)(item % groups) * TE;
     const int lane = threadIdx.x & 63;
-    int64_t na = 0, nb = 0, ni = 0;
-    for (int64_t w = lane; w < W; w += 64) {
-        const uint64_t x = tail_word(plane_or(a, fs.planes, W, w), w, W, tail);
-        const uint64_t y = tail_word(plane_or(b, es.planes, W, w), w, W, tail);
-        na += __popcll(x);
-        nb += __popcll(y);
-        ni += __popcll(x & y);
+    const uint64_t *a = fs.masks + (int64_t)f * fs.planes * W;
+    const uint64_t *b[TE];
+    for (int i = 0; i < TE; ++i)   // past the last one: repeated, not stored
+        b[i] = es.masks + (int64_t)(e0 + i < E ? e0 + i : E - 1) * es.planes * W;
+    // The columns of lists of up to 64 entries, one per lane, are in flight
+    // with the masks.
+    const int32_t *ca = fs.cols + fs.off[f];
+    const int32_t la = fs.off[f + 1] - fs.off[f];
+    const int32_t xa = lane < la ? ca[lane] : 0;
+    const int32_t *cb[TE];
+    int32_t lb[TE], xb[TE];
+    bool short_lists = la <= 64;
+#pragma unroll
+    for (int i = 0; i < TE; ++i) {
+        const int32_t e = e0 + i < E ? e0 + i : E - 1;
+        cb[i] = es.cols + es.off[e];
+        lb[i] = es.off[e + 1] - es.off[e];
+        xb[i] = lane < lb[i] ? cb[i][lane] : 0;
+        short_lists = short_lists && lb[i] <= 64;
+    }
+    // four words per lane in flight; past the end the last word, ignored
+    T na = 0, nb[TE] = {}, ni[TE] = {};
+    constexpr int U = TE == 1 ? 4 : 2;
+    for (int64_t w0 = lane; w0 < W; w0 += 64 * U) {
+        uint64_t x[U], y[TE][U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t w = w0 + 64 * u < W ? w0 + 64 * u : W - 1;
+            x[u] = plane_or<FP>(a, fs.planes, W, w);
+#pragma unroll
+            for (int i = 0; i < TE; ++i) y[i][u] = plane_or<EP>(b[i], es.planes, W, w);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t w = w0 + 64 * u;
+            const uint64_t keep = w < W - 1 ? ~0ull : (w == W - 1 ? tail : 0ull);
+            na += (T)__popcll(x[u] & keep);
+#pragma unroll
+            for (int i = 0; i < TE; ++i) {
+                nb[i] += (T)__popcll(y[i][u] & keep);
+                ni[i] += (T)__popcll(x[u] & y[i][u] & keep);
+            }
+        }
     }
     na = wave_sum(na);
-    nb = wave_sum(nb);
-    ni = wave_sum(ni);
-    const int32_t *ca = fs.cols + fs.off[f], *cb = es.cols + es.off[e];
-    const int32_t la = fs.off[f + 1] - fs.off[f], lb = es.off[e + 1] - es.off[e];
-    int64_t da, sa, db, sb;
-    column_counts(ca, la, cb, lb, &da, &sa);
-    column_counts(cb, lb, ca, la, &db, &sb);   // sb == sa: shared columns counted from B's side
-    if (lane == 0) {
-        const int64_t inter = ni * (sa < sb ? sa : sb);
-        const int64_t uni = na * da + nb * db - inter;
-        J[pair] = uni > 0 ? (double)inter / (double)uni : 0.0;
+    bool first_a = lane < la;   // the lane's found column has not occurred before it
+    if (short_lists)
+        for (int32_t j = 0; j + 1 < la; ++j) {
+            const int32_t c = __builtin_amdgcn_readlane(xa, j);
+            first_a = first_a && !(j < lane && c == xa);
+        }
+#pragma unroll
+    for (int i = 0; i < TE; ++i) {
+        const int32_t e = e0 + i;
+        if (e >= E) break;
+        nb[i] = wave_sum(nb[i]);
+        ni[i] = wave_sum(ni[i]);
+        int32_t da, db, sh;   // distinct columns of each, shared ones
+        if (short_lists) {
+            bool in_b = false, first_b = lane < lb[i];
+            for (int32_t j = 0; j < lb[i]; ++j) {
+                const int32_t c = __builtin_amdgcn_readlane(xb[i], j);
+                in_b |= c == xa;
+                first_b = first_b && !(j < lane && c == xb[i]);
+            }
+            da = __popcll(__ballot(first_a));
+            db = __popcll(__ballot(first_b));
+            sh = __popcll(__ballot(first_a && in_b));
+        } else {
+            int32_t again;   // the shared columns counted from the other side: the same
+            column_counts(ca, la, cb[i], lb[i], &da, &sh);
+            column_counts(cb[i], lb[i], ca, la, &db, &again);
+        }
+        if (lane == 0) {
+            const int64_t inter = (int64_t)ni[i] * sh;
+            const int64_t uni = (int64_t)na * da + (int64_t)nb[i] * db - inter;
+            J[(int64_t)f * E + e] = uni > 0 ? (double)inter / (double)uni : 0.0;
+        }
     }
 }
 
-// scores[0] = recovery, scores[1] = relevance.  One block: the maxima of a
-// chunk of columns (rows) of J are formed in parallel, then added in index
-// order by one thread.
-__global__ __launch_bounds__(kBlock) void scores_kernel(const double *J, int32_t F, int32_t E,
-                                                        double *scores) {
-    __shared__ double s_max[kBlock];
-    double sums[2] = {0.0, 0.0};
-    for (int which = 0; which < 2; ++which) {
-        const int32_t outer = which == 0 ? E : F, inner = which == 0 ? F : E;
-        for (int32_t base = 0; base < outer; base += kBlock) {
-            const int32_t i = base + (int32_t)threadIdx.x;
-            if (i < outer) {
-                double mx = 0.0;
-                for (int32_t j = 0; j < inner; ++j) {
-                    const double v = which == 0 ? J[(int64_t)j * E + i] : J[(int64_t)i * E + j];
-                    mx = v > mx ? v : mx;
-                }
-                s_max[threadIdx.x] = mx;
-            }
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                const int32_t n = outer - base < kBlock ? outer - base : kBlock;
-                for (int32_t t = 0; t < n; ++t) sums[which] += s_max[t];
-            }
-            __syncthreads();
-        }
+// acc + at(0) + at(1) + ... + at(n - 1) in that order, eight reads in flight.
+template <class F>
+__device__ inline double add_in_order(double acc, int32_t n, F &&at) {
+    int32_t t = 0;
+    for (; t + 8 <= n; t += 8) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = at(t + u);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += v[u];
     }
-    if (threadIdx.x == 0) {
+    for (; t < n; ++t) acc += at(t);
+    return acc;
+}
+
+// scores[0] = recovery, scores[1] = relevance.  One block: the maxima of a
+// chunk of columns or rows of J are formed in parallel, then added in index
+// order by one thread.  Recovery: kScoreCols columns at a time, each by the
+// threads of its residue, whose maxima (bit patterns of values >= 0 order
+// as integers) meet in LDS.  Relevance: kScoreRow lanes to a row.  Bound by
+// latency (and by the ordered sum, one FP64 addition after the other, for
+// long lists): 100 x 20 took 27.8 us with one thread per maximum, and takes
+// 4.1 us.
+constexpr int kScoreBlock = 1024;
+constexpr int kScoreCols = 512;     // columns of a recovery chunk
+constexpr int kScoreRow = 8;        // lanes per row of a relevance chunk
+constexpr int kScoreRows = kScoreBlock / kScoreRow;
+__global__ __launch_bounds__(kScoreBlock) void scores_kernel(const double *J, int32_t F, int32_t E,
+                                                             double *scores) {
+    __shared__ unsigned long long s_max[kScoreCols];
+    __shared__ double s_row[kScoreRows];
+    const int tid = threadIdx.x;
+    double recovery = 0.0, relevance = 0.0;
+    for (int32_t base = 0; base < E; base += kScoreCols) {
+        const int32_t n = E - base < kScoreCols ? E - base : kScoreCols;
+        if (tid < kScoreCols) s_max[tid] = 0ull;
+        __syncthreads();
+        const int32_t g = tid / n, c = tid - g * n, groups = kScoreBlock / n;
+        if (g < groups) {
+            double mx = 0.0;
+            for (int32_t f = g; f < F; f += 8 * groups) {
+                double v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int32_t r = f + u * groups;
+                    v[u] = r < F ? J[(int64_t)r * E + base + c] : 0.0;
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) mx = v[u] > mx ? v[u] : mx;
+            }
+            atomicMax(&s_max[c], (unsigned long long)__double_as_longlong(mx));
+        }
+        __syncthreads();
+        if (tid == 0)
+            recovery = add_in_order(recovery, n, [&](int32_t t) {
+                return __longlong_as_double((long long)s_max[t]);
+            });
+        __syncthreads();
+    }
+    for (int32_t base = 0; base < F; base += kScoreRows) {
+        const int32_t n = F - base < kScoreRows ? F - base : kScoreRows;
+        const int32_t r = tid / kScoreRow, q = tid % kScoreRow;
+        double mx = 0.0;
+        if (r < n)
+            for (int32_t e = q; e < E; e += 8 * kScoreRow) {
+                double v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int32_t x = e + u * kScoreRow;
+                    v[u] = x < E ? J[(int64_t)(base + r) * E + x] : 0.0;
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) mx = v[u] > mx ? v[u] : mx;
+            }
+        for (int d = kScoreRow / 2; d >= 1; d >>= 1) {
+            const double o = __shfl_xor(mx, d);
+            mx = o > mx ? o : mx;
+        }
+        if (q == 0) s_row[r] = mx;
+        __syncthreads();
+        if (tid == 0)
+            relevance = add_in_order(relevance, n, [&](int32_t t) { return s_row[t]; });
+        __syncthreads();
+    }
+    if (tid == 0) {
         const bool none = F == 0 || E == 0;
-        scores[0] = none ? 0.0 : sums[0] / (double)E;
-        scores[1] = none ? 0.0 : sums[1] / (double)F;
+        scores[0] = none ? 0.0 : recovery / (double)E;
+        scores[1] = none ? 0.0 : relevance / (double)F;
     }
 }
 
@@ -258,15 +453,24 @@ ebic_status ebic_mask_rows(const uint64_t *d_masks, int32_t K, int32_t planes, i
     hipError_t e;
     if (K > 0) {
         // With no rows (W = 0) every count is 0 and the masks are not read.
-        hipLaunchKernelGGL(mask_count_kernel, dim3((unsigned)K), dim3(kBlock), 0, s, d_masks,
-                           planes, W, tail_mask(n_rows), d_offsets);
+        for_planes(planes, [&](auto pl) {
+            hipLaunchKernelGGL((mask_count_kernel<decltype(pl)::value>), dim3((unsigned)K),
+                               dim3(kBlock), 0, s, d_masks, planes, W, tail_mask(n_rows),
+                               d_offsets);
+        });
         if ((e = hipGetLastError()) != hipSuccess) return hip_error(e, "mask_count_kernel");
     }
     hipLaunchKernelGGL(offsets_scan_kernel, dim3(1), dim3(kBlock), 0, s, d_offsets, K);
     if ((e = hipGetLastError()) != hipSuccess) return hip_error(e, "offsets_scan_kernel");
-    if (K > 0 && W > 0) {
-        hipLaunchKernelGGL(mask_scatter_kernel, dim3((unsigned)K), dim3(kBlock), 0, s, d_masks,
-                           planes, W, tail_mask(n_rows), d_offsets, d_rows, rows_capacity);
+    if (K > 0 && W > 0 && rows_capacity > 0) {
+        int64_t chunk = (W + kScatterChunks - 1) / kScatterChunks;
+        chunk = (chunk + kScatterWords - 1) / kScatterWords * kScatterWords;
+        const dim3 grid((unsigned)K, (unsigned)((W + chunk - 1) / chunk));
+        for_planes(planes, [&](auto pl) {
+            hipLaunchKernelGGL((mask_scatter_kernel<decltype(pl)::value>), grid, dim3(kBlock), 0,
+                               s, d_masks, planes, W, tail_mask(n_rows), d_offsets, d_rows,
+                               rows_capacity, chunk);
+        });
         if ((e = hipGetLastError()) != hipSuccess) return hip_error(e, "mask_scatter_kernel");
     }
     return EBIC_OK;
@@ -289,12 +493,32 @@ ebic_status ebic_match_scores(const ebic_bicluster_set *found, const ebic_biclus
     if (F * E > 0) {
         SetView fs{found->row_masks, found->planes, found->col_offsets, found->cols};
         SetView es{expected->row_masks, expected->planes, expected->col_offsets, expected->cols};
-        const int64_t blocks = (F * E + kWaves - 1) / kWaves;
-        hipLaunchKernelGGL(jaccard_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, s, fs,
-                           (int32_t)F, es, (int32_t)E, W, tail_mask(n_rows), d_jaccard);
+        // Four expected biclusters to a wave once that still leaves each of
+        // the GPU's 1024 SIMDs a wave (120 x 60 biclusters of 50000 rows:
+        // 16.0 us, 18.4 with one); one otherwise, where more waves hide more
+        // latency (100 x 20 of 20000 rows: 8.3 us, 11.6 with four).
+        const bool tiled = F * ((E + 3) / 4) >= 1024;
+        const int64_t waves = F * (tiled ? (E + 3) / 4 : E);
+        const int64_t blocks = (waves + kWaves - 1) / kWaves;
+        auto launch = [&](auto type, auto te) {
+            for_planes(found->planes, [&](auto fp) {
+                for_planes(expected->planes, [&](auto ep) {
+                    hipLaunchKernelGGL((jaccard_kernel<decltype(type), decltype(te)::value,
+                                                       decltype(fp)::value, decltype(ep)::value>),
+                                       dim3((unsigned)blocks), dim3(kBlock), 0, s, fs, (int32_t)F,
+                                       es, (int32_t)E, W, tail_mask(n_rows), d_jaccard);
+                });
+            });
+        };
+        using one = std::integral_constant<int, 1>;
+        using four = std::integral_constant<int, 4>;
+        if (n_rows > INT32_MAX)
+            tiled ? launch(int64_t{}, four{}) : launch(int64_t{}, one{});
+        else
+            tiled ? launch(int32_t{}, four{}) : launch(int32_t{}, one{});
         if ((e = hipGetLastError()) != hipSuccess) return hip_error(e, "jaccard_kernel");
     }
-    hipLaunchKernelGGL(scores_kernel, dim3(1), dim3(kBlock), 0, s, d_jaccard, (int32_t)F,
+    hipLaunchKernelGGL(scores_kernel, dim3(1), dim3(kScoreBlock), 0, s, d_jaccard, (int32_t)F,
                        (int32_t)E, d_scores);
     if ((e = hipGetLastError()) != hipSuccess) return hip_error(e, "scores_kernel");
     return EBIC_OK;
