@@ -77,7 +77,7 @@ struct FusedRows {
     const float *b1, *b2, *b3;
     const float *target;             // nullptr: forward only (y)
     float *y, *sq;
-    uint16_t *XrT, *H1rT, *dZ2rT, *dZ1rT;   // feature-major [features][Bp]
+    uint16_t *XrT, *H1rT, *dZ2rT, *dZ1rT;   // tile-major [Bp / tile rows][features][tile rows]
     float *dX;                       // [Bp][2D]
     float *pw3, *pb2, *pb1, *pb3;    // per row tile: [tiles][H] (pb3: [tiles])
 };

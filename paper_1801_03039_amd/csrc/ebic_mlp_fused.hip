@@ -6,7 +6,7 @@
 //                         per-candidate backward pass (dz2, dz1, dx), with
 //                         the tile's activations kept in LDS; writes the
 //                         BF16 operands of the weight gradients transposed
-//                         (feature-major, candidates contiguous) and each
+//                         (tile-major, candidates contiguous) and each
 //                         tile's partial bias/output-weight gradient sums
 //   B  mlp_grads_kernel   weight gradients as split-K products over the
 //                         batch (one partial per 256 candidates), the bias
@@ -24,9 +24,19 @@
 // are those of the layer-by-layer kernels: bf16(x), bf16(relu(z1)),
 // bf16(relu(z2)), bf16(dz2), bf16(dz1), weights read as BF16 copies.  Every
 // sum has a fixed order, so a step is deterministic on one device.
+//
+// What bounds a step (B = 8192, 500 columns: A 32.5 us, B 18.6, C 4.2; 38.2,
+// 34.1 and 4.2 before): the products are small, and each launch lasts as long
+// as its workgroups' chains of dependent loads.  A's tile of 32 candidates is
+// one workgroup of 8 waves (with 4 waves 38.2 us; with each layer's weights
+// loaded whole, a phase ahead, 38.3, since 140 VGPRs leave one workgroup per
+// compute unit and the loads gain nothing), B's operands are stored tile by
+// tile (30.2 us with rows of the whole batch, whose fragments met in the same
+// cache channels).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "ebic_mlp.h"
 
@@ -35,10 +45,12 @@ namespace mlp {
 namespace {
 
 constexpr int kBlock = 256;
+constexpr int kRowsBlock = 512;        // lanes of a row tile's workgroup
 constexpr int kTB = 32;                // candidates per row tile
 constexpr int kD = 32, kD2 = 64, kH = 256;
 constexpr int kLdX = kD2 + 8, kLdH = kH + 8;   // LDS row strides (bf16), 16-byte aligned rows
 constexpr int kChunk = 256;            // candidates per weight-gradient partial
+static_assert(kTB == 32 && kChunk % kTB == 0, "one MFMA step of candidates per tile");
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -84,16 +96,18 @@ struct RowsLds {
     uint16_t dz2[kTB][kLdH];
     uint16_t dz1[kTB][kLdH];
     uint8_t m1[kTB][kH];
-    float yp[4][kTB];
+    float yp[kRowsBlock / 128][kTB];
     float dy[kTB];
 };
 
-// Copies a [32][W] LDS tile to a feature-major global matrix dst[W][Bp]
-// (columns b0 .. b0 + 31), 16 bytes per store.
+// Copies a [32][W] LDS tile to its place in a tile-major global matrix
+// [tile][W][32] (features of a tile of candidates, candidates contiguous),
+// 16 bytes per store, neighbouring lanes next to each other.
 template <int W, int LD>
 __device__ __forceinline__ void store_transposed(const uint16_t (*src)[LD], uint16_t *dst,
-                                                 int64_t Bp, int64_t b0) {
-    for (int i = threadIdx.x; i < W * (kTB / 8); i += kBlock) {
+                                                 int64_t tile) {
+    dst += tile * (W * kTB);
+    for (int i = threadIdx.x; i < W * (kTB / 8); i += kRowsBlock) {
         const int w = i / (kTB / 8), c = i % (kTB / 8);
         uint16_t v[8];
 #pragma unroll
@@ -103,14 +117,42 @@ __device__ __forceinline__ void store_transposed(const uint16_t (*src)[LD], uint
         q.y = v[2] | ((uint32_t)v[3] << 16);
         q.z = v[4] | ((uint32_t)v[5] << 16);
         q.w = v[6] | ((uint32_t)v[7] << 16);
-        *reinterpret_cast<uint4 *>(dst + (int64_t)w * Bp + b0 + c * 8) = q;
+        *reinterpret_cast<uint4 *>(dst + w * kTB + c * 8) = q;
     }
 }
 
-__global__ __launch_bounds__(kBlock) void mlp_rows_kernel(FusedRows a) {
+__global__ __launch_bounds__(kRowsBlock) void mlp_rows_kernel(FusedRows a) {
     __shared__ RowsLds S;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t b0 = (int64_t)blockIdx.x * kTB;
+    constexpr int kC = 2;   // 16-column blocks per wave
+    // acc += A W^T for the wave's columns 32 wv .. 32 wv + 31: A (32 x K) in
+    // LDS, the fragments of the weight copy W two k-steps ahead of their use.
+    auto product = [&](auto k_size, const uint16_t *A, int ld, const uint16_t *W,
+                       f32x4 (&acc)[2][kC]) {
+        constexpr int K = decltype(k_size)::value, KS = K / 32, kAhead = KS < 2 ? KS : 2;
+        bf16x8 w[kAhead][kC];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k)
+#pragma unroll
+            for (int c = 0; c < kC; ++c) w[k][c] = frag(W, K, 32 * wv + 16 * c, 32 * k, lane);
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            bf16x8 now[kC];
+#pragma unroll
+            for (int c = 0; c < kC; ++c) {
+                now[c] = w[k % kAhead][c];
+                if (k + kAhead < KS)
+                    w[k % kAhead][c] = frag(W, K, 32 * wv + 16 * c, 32 * (k + kAhead), lane);
+            }
+#pragma unroll
+            for (int rb = 0; rb < 2; ++rb) {
+                const bf16x8 fa = frag(A, ld, 16 * rb, 32 * k, lane);
+#pragma unroll
+                for (int c = 0; c < kC; ++c) acc[rb][c] = mfma(fa, now[c], acc[rb][c]);
+            }
+        }
+    };
 
     // pooling: x = [mean E + Z[L] ; mean of F[c_t] * T[c_{t+1}]], bf16(x).
     // The tile's series are staged in LDS.
@@ -120,58 +162,48 @@ __global__ __launch_bounds__(kBlock) void mlp_rows_kernel(FusedRows a) {
     }
     __syncthreads();
     const int32_t base = S.off[0], n_cols = S.off[kTB] - base;
-    for (int i = tid; i < n_cols && i < kTileCols; i += kBlock) S.cols[i] = a.cols[base + i];
+    for (int i = tid; i < n_cols && i < kTileCols; i += kRowsBlock) S.cols[i] = a.cols[base + i];
     __syncthreads();
     {
-        // thread = (candidate r, 8 consecutive dimensions 8q .. 8q + 7 of x):
-        // q < 4 pools E, q >= 4 the pair products F * T; four series
+        // thread = (candidate r, 4 consecutive dimensions 4q .. 4q + 3 of x):
+        // q < 8 pools E, q >= 8 the pair products F * T; ten series
         // positions' loads in flight at a time, sums in series order
-        const int r = tid / 8, q = tid % 8;
-        const bool pair = q >= kD / 8;
-        const int d0 = 8 * (pair ? q - kD / 8 : q);
+        const int r = tid / 16, q = tid % 16;
+        const bool pair = q >= kD / 4;
+        const int d0 = 4 * (pair ? q - kD / 4 : q);
         const int32_t s = S.off[r], e = S.off[r + 1], L = e - s;
         const bool staged = n_cols <= kTileCols;
         auto col = [&](int32_t t) -> int32_t { return staged ? S.cols[t - base] : a.cols[t]; };
-        float acc[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc[u] = 0.f;
+        float acc[4] = {0.f, 0.f, 0.f, 0.f};
         const int32_t n_terms = pair ? L - 1 : L;
-        for (int32_t t0 = 0; t0 < n_terms; t0 += 4) {
-            float4 v[4][2];
+        constexpr int kAhead = 10;
+        for (int32_t t0 = 0; t0 < n_terms; t0 += kAhead) {
+            float4 v[kAhead], w[kAhead];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
+            for (int j = 0; j < kAhead; ++j) {
                 const int32_t t = t0 + j;
-                v[j][0] = v[j][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+                v[j] = w[j] = make_float4(0.f, 0.f, 0.f, 0.f);
                 if (t < n_terms) {
                     const int32_t c = col(s + t);
-                    if (!pair) {
-                        const float4 *er = reinterpret_cast<const float4 *>(a.E + (int64_t)c * kD + d0);
-                        v[j][0] = er[0];
-                        v[j][1] = er[1];
-                    } else {
-                        const int32_t c2 = col(s + t + 1);
-                        const float4 *fr = reinterpret_cast<const float4 *>(a.F + (int64_t)c * kD + d0);
-                        const float4 *tr = reinterpret_cast<const float4 *>(a.T + (int64_t)c2 * kD + d0);
-                        const float4 f0 = fr[0], f1 = fr[1], u0 = tr[0], u1 = tr[1];
-                        v[j][0] = make_float4(f0.x * u0.x, f0.y * u0.y, f0.z * u0.z, f0.w * u0.w);
-                        v[j][1] = make_float4(f1.x * u1.x, f1.y * u1.y, f1.z * u1.z, f1.w * u1.w);
-                    }
+                    const float *table = pair ? a.F : a.E;
+                    v[j] = *reinterpret_cast<const float4 *>(table + (int64_t)c * kD + d0);
+                    if (pair)
+                        w[j] = *reinterpret_cast<const float4 *>(
+                            a.T + (int64_t)col(s + t + 1) * kD + d0);
                 }
             }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                acc[0] += v[j][0].x;
-                acc[1] += v[j][0].y;
-                acc[2] += v[j][0].z;
-                acc[3] += v[j][0].w;
-                acc[4] += v[j][1].x;
-                acc[5] += v[j][1].y;
-                acc[6] += v[j][1].z;
-                acc[7] += v[j][1].w;
+            for (int j = 0; j < kAhead; ++j) {
+                if (pair) v[j] = make_float4(v[j].x * w[j].x, v[j].y * w[j].y, v[j].z * w[j].z,
+                                             v[j].w * w[j].w);
+                acc[0] += v[j].x;
+                acc[1] += v[j].y;
+                acc[2] += v[j].z;
+                acc[3] += v[j].w;
             }
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < 4; ++u) {
             float x = 0.f;
             if (b0 + r < a.B) {
                 if (!pair) x = acc[u] / (float)L + a.Zl[(int64_t)L * kD + d0 + u];
@@ -182,24 +214,13 @@ __global__ __launch_bounds__(kBlock) void mlp_rows_kernel(FusedRows a) {
     }
     __syncthreads();
 
-    // layer 1: z1 = bf16(x) W1^T + b1 (wave wv: columns 64 wv .. 64 wv + 63)
+    // layer 1: z1 = bf16(x) W1^T + b1 (wave wv: columns 32 wv .. 32 wv + 31)
     {
-        f32x4 acc[2][4] = {};
+        f32x4 acc[2][kC] = {};
+        product(std::integral_constant<int, kD2>{}, &S.x[0][0], kLdX, a.W1b, acc);
 #pragma unroll
-        for (int k0 = 0; k0 < kD2; k0 += 32) {
-            bf16x8 fa[2], fb[4];
-#pragma unroll
-            for (int rb = 0; rb < 2; ++rb) fa[rb] = frag(&S.x[0][0], kLdX, 16 * rb, k0, lane);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) fb[c] = frag(a.W1b, kD2, 64 * wv + 16 * c, k0, lane);
-#pragma unroll
-            for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) acc[rb][c] = mfma(fa[rb], fb[c], acc[rb][c]);
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int n = 64 * wv + 16 * c + (lane & 15);
+        for (int c = 0; c < kC; ++c) {
+            const int n = 32 * wv + 16 * c + (lane & 15);
             const float bias = a.b1[n];
 #pragma unroll
             for (int rb = 0; rb < 2; ++rb)
@@ -214,49 +235,59 @@ __global__ __launch_bounds__(kBlock) void mlp_rows_kernel(FusedRows a) {
     }
     __syncthreads();
 
-    // layer 2: z2 = bf16(h1) W2^T + b2; h2 = bf16(relu(z2)) kept in registers
-    float h2[2][4][4], m2[2][4][4];
+    // layer 2: z2 = bf16(h1) W2^T + b2; h2 = bf16(relu(z2)) kept in
+    // registers, [z2 > 0] as bits of m2
+    float h2[2][kC][4];
+    uint32_t m2 = 0;
+    auto bit2 = [](int rb, int c, int v) { return (rb * kC + c) * 4 + v; };
     {
-        f32x4 acc[2][4] = {};
-        bf16x8 fb[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) fb[c] = frag(a.W2b, kH, 64 * wv + 16 * c, 0, lane);
-        for (int k0 = 0; k0 < kH; k0 += 32) {
-            bf16x8 fa[2], nb[4];
-            const int k1 = k0 + 32 < kH ? k0 + 32 : k0;   // next step's weights in flight
-#pragma unroll
-            for (int c = 0; c < 4; ++c) nb[c] = frag(a.W2b, kH, 64 * wv + 16 * c, k1, lane);
-#pragma unroll
-            for (int rb = 0; rb < 2; ++rb) fa[rb] = frag(&S.h1[0][0], kLdH, 16 * rb, k0, lane);
-#pragma unroll
-            for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) acc[rb][c] = mfma(fa[rb], fb[c], acc[rb][c]);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) fb[c] = nb[c];
-        }
+        f32x4 acc[2][kC] = {};
+        product(std::integral_constant<int, kH>{}, &S.h1[0][0], kLdH, a.W2b, acc);
+        // The output product adds 64 columns per lane group, 16 apart, in
+        // column order: the even wave of a pair hands its partial sums of the
+        // first 32 to the odd one through LDS (dz2 is not in use yet).
         float yp[2][4] = {};
+        float *const hand = reinterpret_cast<float *>(&S.dz2[0][0]) + (wv >> 1) * 8 * 64;
+        auto add_columns = [&]() {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int n = 64 * wv + 16 * c + (lane & 15);
-            const float bias = a.b2[n], w3 = from_bf16(a.w3b[n]);
+            for (int c = 0; c < kC; ++c) {
+                const float w3 = from_bf16(a.w3b[32 * wv + 16 * c + (lane & 15)]);
+#pragma unroll
+                for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) yp[rb][v] += h2[rb][c][v] * w3;
+            }
+        };
+#pragma unroll
+        for (int c = 0; c < kC; ++c) {
+            const float bias = a.b2[32 * wv + 16 * c + (lane & 15)];
 #pragma unroll
             for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const float z = acc[rb][c][v] + bias;
                     h2[rb][c][v] = from_bf16(to_bf16(fmaxf(z, 0.f)));
-                    m2[rb][c][v] = z > 0.f ? 1.f : 0.f;
-                    yp[rb][v] += h2[rb][c][v] * w3;
+                    m2 |= (z > 0.f ? 1u : 0u) << bit2(rb, c, v);
                 }
         }
+        if ((wv & 1) == 0) {
+            add_columns();
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
+            for (int i = 0; i < 8; ++i) hand[i * 64 + lane] = yp[i >> 2][i & 3];
+        }
+        __syncthreads();
+        if (wv & 1) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float s = sum_row(yp[rb][v]);
-                if ((lane & 15) == 0) S.yp[wv][16 * rb + 4 * (lane >> 4) + v] = s;
-            }
+            for (int i = 0; i < 8; ++i) yp[i >> 2][i & 3] = hand[i * 64 + lane];
+            add_columns();
+#pragma unroll
+            for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float s = sum_row(yp[rb][v]);
+                    if ((lane & 15) == 0) S.yp[wv >> 1][16 * rb + 4 * (lane >> 4) + v] = s;
+                }
+        }
     }
     __syncthreads();
     if (tid < kTB) {
@@ -280,8 +311,8 @@ __global__ __launch_bounds__(kBlock) void mlp_rows_kernel(FusedRows a) {
     // (b2), h2 dy (w3) and dy (b3); bf16(dz2) to LDS
     const int64_t tile = blockIdx.x;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const int n = 64 * wv + 16 * c + (lane & 15);
+    for (int c = 0; c < kC; ++c) {
+        const int n = 32 * wv + 16 * c + (lane & 15);
         const float w3 = from_bf16(a.w3b[n]);
         float sb2 = 0.f, sw3 = 0.f;
 #pragma unroll
@@ -290,7 +321,7 @@ __global__ __launch_bounds__(kBlock) void mlp_rows_kernel(FusedRows a) {
             for (int v = 0; v < 4; ++v) {
                 const int r = 16 * rb + 4 * (lane >> 4) + v;
                 const float dy = S.dy[r];
-                const float g = m2[rb][c][v] != 0.f ? dy * w3 : 0.f;
+                const float g = (m2 >> bit2(rb, c, v)) & 1u ? dy * w3 : 0.f;
                 sb2 += g;
                 sw3 += h2[rb][c][v] * dy;
                 S.dz2[r][n] = to_bf16(g);
@@ -310,28 +341,16 @@ __global__ __launch_bounds__(kBlock) void mlp_rows_kernel(FusedRows a) {
     __syncthreads();
 
     // dz1 = (bf16(dz2) W2) [z1 > 0]; per-tile sums (b1); bf16(dz1) to LDS
+    const int cb = wv & 3, rbx = wv >> 2;   // the wave's block of dx
+    bf16x8 w1t[kH / 32];
     {
-        f32x4 acc[2][4] = {};
-        bf16x8 fb[4];
+        f32x4 acc[2][kC] = {};
+        product(std::integral_constant<int, kH>{}, &S.dz2[0][0], kLdH, a.W2bT, acc);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) fb[c] = frag(a.W2bT, kH, 64 * wv + 16 * c, 0, lane);
-        for (int k0 = 0; k0 < kH; k0 += 32) {
-            bf16x8 fa[2], nb[4];
-            const int k1 = k0 + 32 < kH ? k0 + 32 : k0;
+        for (int k = 0; k < kH / 32; ++k) w1t[k] = frag(a.W1bT, kH, 16 * cb, 32 * k, lane);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) nb[c] = frag(a.W2bT, kH, 64 * wv + 16 * c, k1, lane);
-#pragma unroll
-            for (int rb = 0; rb < 2; ++rb) fa[rb] = frag(&S.dz2[0][0], kLdH, 16 * rb, k0, lane);
-#pragma unroll
-            for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) acc[rb][c] = mfma(fa[rb], fb[c], acc[rb][c]);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) fb[c] = nb[c];
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int n = 64 * wv + 16 * c + (lane & 15);
+        for (int c = 0; c < kC; ++c) {
+            const int n = 32 * wv + 16 * c + (lane & 15);
             float sb1 = 0.f;
 #pragma unroll
             for (int rb = 0; rb < 2; ++rb)
@@ -348,54 +367,57 @@ __global__ __launch_bounds__(kBlock) void mlp_rows_kernel(FusedRows a) {
     }
     __syncthreads();
 
-    // dx = bf16(dz1) W1 (wave wv: columns 16 wv .. 16 wv + 15)
+    // dx = bf16(dz1) W1 (wave wv: columns 16 (wv mod 4) .. + 15 of rows
+    // 16 (wv / 4) .. + 15)
     {
-        f32x4 acc[2] = {};
-        bf16x8 fb[kH / 32];
-#pragma unroll
-        for (int k = 0; k < kH / 32; ++k) fb[k] = frag(a.W1bT, kH, 16 * wv, 32 * k, lane);
+        f32x4 acc = {};
 #pragma unroll
         for (int k = 0; k < kH / 32; ++k)
+            acc = mfma(frag(&S.dz1[0][0], kLdH, 16 * rbx, 32 * k, lane), w1t[k], acc);
+        const int d = 16 * cb + (lane & 15);
 #pragma unroll
-            for (int rb = 0; rb < 2; ++rb)
-                acc[rb] = mfma(frag(&S.dz1[0][0], kLdH, 16 * rb, 32 * k, lane), fb[k], acc[rb]);
-        const int d = 16 * wv + (lane & 15);
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int64_t b = b0 + 16 * rb + 4 * (lane >> 4) + v;
-                a.dX[b * kD2 + d] = acc[rb][v];
-            }
+        for (int v = 0; v < 4; ++v) {
+            const int64_t b = b0 + 16 * rbx + 4 * (lane >> 4) + v;
+            a.dX[b * kD2 + d] = acc[v];
+        }
     }
-    // the weight-gradient operands, feature-major
-    store_transposed<kD2, kLdX>(S.x, a.XrT, a.Bp, b0);
-    store_transposed<kH, kLdH>(S.h1, a.H1rT, a.Bp, b0);
-    store_transposed<kH, kLdH>(S.dz2, a.dZ2rT, a.Bp, b0);
-    store_transposed<kH, kLdH>(S.dz1, a.dZ1rT, a.Bp, b0);
+    // the weight-gradient operands
+    store_transposed<kD2, kLdX>(S.x, a.XrT, tile);
+    store_transposed<kH, kLdH>(S.h1, a.H1rT, tile);
+    store_transposed<kH, kLdH>(S.dz2, a.dZ2rT, tile);
+    store_transposed<kH, kLdH>(S.dz1, a.dZ1rT, tile);
 }
 
 // ------------------------------------------------------------- kernel B --
 
 // One 64 x 64 tile of a split-K product over a chunk of 256 candidates:
-// out[m][n] = sum_b A[m][b] Bm[n][b], A and Bm feature-major (row stride
-// Bp); four waves of 32 x 32.
-__device__ void grad_tile(const uint16_t *A, const uint16_t *Bm, int64_t Bp, int64_t m0,
-                          int64_t n0, int64_t kb, float *out, int64_t ldo) {
+// out[m][n] = sum_b A[m][b] Bm[n][b], A and Bm tile-major (MA and MB
+// features, kTB candidates per tile: a fragment is 1 KiB of consecutive
+// memory); four waves of 32 x 32.
+template <int MA, int MB>
+__device__ void grad_tile(const uint16_t *A, const uint16_t *Bm, int64_t m0, int64_t n0,
+                          int64_t kb, float *out, int64_t ldo) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t mw = m0 + 32 * (wv >> 1), nw = n0 + 32 * (wv & 1);
     f32x4 acc[2][2] = {};
-    for (int64_t k0 = kb; k0 < kb + kChunk; k0 += 32) {
-        bf16x8 fa[2], fb[2];
+    constexpr int kSteps = kChunk / 32;
+    constexpr int kAhead = 4;   // k-steps in flight (all 8 cost a wave per SIMD)
+    for (int k0 = 0; k0 < kSteps; k0 += kAhead) {
+        bf16x8 fa[kAhead][2], fb[kAhead][2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            fa[i] = frag(A, Bp, mw + 16 * i, k0, lane);
-            fb[i] = frag(Bm, Bp, nw + 16 * i, k0, lane);
-        }
+        for (int k = 0; k < kAhead; ++k)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < 2; ++i) {
+                const int64_t tile = kb / kTB + k0 + k;
+                fa[k][i] = frag(A + tile * (MA * kTB), kTB, mw + 16 * i, 0, lane);
+                fb[k][i] = frag(Bm + tile * (MB * kTB), kTB, nw + 16 * i, 0, lane);
+            }
 #pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = mfma(fa[i], fb[j], acc[i][j]);
+        for (int k = 0; k < kAhead; ++k)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = mfma(fa[k][i], fb[k][j], acc[i][j]);
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -407,31 +429,120 @@ __device__ void grad_tile(const uint16_t *A, const uint16_t *Bm, int64_t Bp, int
                     acc[i][j][v];
 }
 
-// Fixed-order sum of the kBlock threads' vectors v[0..kD) into out (thread
-// c < kD writes out[c]): threads' rows of 32 are added in order, then the
-// eight rows.  red holds kBlock x kD floats.
-__device__ void block_sum(const float (&v)[kD], float *red, float *out) {
-    const int tid = threadIdx.x;
-#pragma unroll
-    for (int c = 0; c < kD; ++c) red[tid * kD + c] = v[c];
+// Embedding gradients.  A list (a column's occurrences, a length's
+// candidates) is summed in a fixed order: entry o belongs to row
+// (o / 32) mod 8, place o mod 32; entries of one row and place are added
+// first (list order), then a row's 32 places, then the 8 rows.  Half-wave =
+// row, lane = embedding dimension, so that every read of a table row is one
+// 128-byte line; what the entries of the 32 places need is loaded first, a
+// place per lane, and passed on by lane exchanges.  (With an entry per thread and
+// its 96 sums in registers, 212 VGPRs and three reductions through LDS, whose
+// rows met in two banks, these jobs took most of the kernel's 34 us.)
+constexpr int kRows = kBlock / kD;     // 8
+constexpr int kPlaces = 8;            // places whose loads are in flight
+static_assert(kRows * kD == kBlock && kD == 32, "half-waves are rows");
+
+// The rows' sums acc of one dimension each -> out[0..kD).
+__device__ void row_sums(float acc, float *red, float *out) {
+    red[threadIdx.x] = acc;
     __syncthreads();
-    constexpr int kGroups = kBlock / kD;          // 8 groups of 32 threads' vectors
-    const int r = tid / kD, c = tid % kD;         // thread: group r, dimension c
-    float acc = 0.f;
-    for (int k = 0; k < kBlock / kGroups; ++k) acc += red[(r * (kBlock / kGroups) + k) * kD + c];
-    __syncthreads();
-    red[r * kD + c] = acc;
-    __syncthreads();
-    if (tid < kD) {
+    if (threadIdx.x < kD) {
         float s = 0.f;
-        for (int k = 0; k < kGroups; ++k) s += red[k * kD + tid];
-        out[tid] = s;
+        for (int k = 0; k < kRows; ++k) s += red[k * kD + threadIdx.x];
+        out[threadIdx.x] = s;
     }
     __syncthreads();
 }
 
+// Column j: dE from its occurrences' dx / L, dF and dT from the pairs it
+// begins and ends.
+__device__ void column_grads(const FusedGrads &g, int32_t j, float *red) {
+    const int r = threadIdx.x / kD, c = threadIdx.x % kD;
+    const int32_t o0 = g.occ_start[j], o1 = g.occ_start[j + 1];
+    float ae = 0.f, af = 0.f, at = 0.f;
+    const int32_t row0 = o0 + r * kD;
+    // lane c: what the entry at place c of the row's round at `o` needs
+    int32_t b, next, prev;
+    float inv_l, inv;
+    auto entry = [&](int32_t o) {
+        const int32_t mine = o + c < o1 ? o + c : o1 - 1;
+        const int32_t pos = g.occ_pos[mine];
+        b = g.occ_b[mine];
+        const int32_t s = g.off[b], e = g.off[b + 1], L = e - s;
+        next = pos + 1 < e ? g.cols[pos + 1] : -1;
+        prev = pos > s ? g.cols[pos - 1] : -1;
+        inv_l = 1.f / (float)L;
+        inv = L > 1 ? 1.f / (float)(L - 1) : 0.f;
+    };
+    if (row0 < o1) entry(row0);
+    for (int p0 = 0; p0 < kD && row0 + p0 < o1; p0 += kPlaces) {
+        float ve[kPlaces], vf[kPlaces], vt[kPlaces];
+#pragma unroll
+        for (int u = 0; u < kPlaces; ++u) ve[u] = vf[u] = vt[u] = 0.f;
+        for (int32_t o = row0; o + p0 < o1; o += kBlock) {
+            if (o != row0 || (p0 > 0 && row0 + kBlock < o1)) entry(o);
+            float xe[kPlaces], xp[kPlaces], tn[kPlaces], fp[kPlaces];
+#pragma unroll
+            for (int u = 0; u < kPlaces; ++u) {
+                const int32_t bu = __shfl(b, p0 + u, kD);
+                const int32_t nu = __shfl(next, p0 + u, kD), pu = __shfl(prev, p0 + u, kD);
+                xe[u] = g.dX[(int64_t)bu * kD2 + c];
+                xp[u] = g.dX[(int64_t)bu * kD2 + kD + c];
+                tn[u] = g.T[(int64_t)(nu < 0 ? 0 : nu) * kD + c];
+                fp[u] = g.F[(int64_t)(pu < 0 ? 0 : pu) * kD + c];
+            }
+#pragma unroll
+            for (int u = 0; u < kPlaces; ++u) {
+                const float il = __shfl(inv_l, p0 + u, kD), iv = __shfl(inv, p0 + u, kD);
+                const bool has_next = __shfl(next, p0 + u, kD) >= 0;
+                const bool has_prev = __shfl(prev, p0 + u, kD) >= 0;
+                if (o + p0 + u < o1) {
+                    ve[u] += xe[u] * il;
+                    if (has_next) vf[u] += xp[u] * tn[u] * iv;
+                    if (has_prev) vt[u] += xp[u] * fp[u] * iv;
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kPlaces; ++u) {
+            ae += ve[u];
+            af += vf[u];
+            at += vt[u];
+        }
+    }
+    row_sums(ae, red, g.gE + (int64_t)j * kD);
+    row_sums(af, red, g.gF + (int64_t)j * kD);
+    row_sums(at, red, g.gT + (int64_t)j * kD);
+}
+
+// Length l: dZ from its candidates' dx.
+__device__ void length_grads(const FusedGrads &g, int32_t l, float *red) {
+    const int r = threadIdx.x / kD, c = threadIdx.x % kD;
+    const int32_t o0 = g.len_start[l], o1 = g.len_start[l + 1];
+    const int32_t row0 = o0 + r * kD;
+    float acc = 0.f;
+    for (int p0 = 0; p0 < kD && row0 + p0 < o1; p0 += kPlaces) {
+        float v[kPlaces];
+#pragma unroll
+        for (int u = 0; u < kPlaces; ++u) v[u] = 0.f;
+        for (int32_t o = row0; o + p0 < o1; o += kBlock) {
+            const int32_t b = g.len_b[o + c < o1 ? o + c : o1 - 1];   // lane c: place c
+            float x[kPlaces];
+#pragma unroll
+            for (int u = 0; u < kPlaces; ++u)
+                x[u] = g.dX[(int64_t)__shfl(b, p0 + u, kD) * kD2 + c];
+#pragma unroll
+            for (int u = 0; u < kPlaces; ++u)
+                if (o + p0 + u < o1) v[u] += x[u];
+        }
+#pragma unroll
+        for (int u = 0; u < kPlaces; ++u) acc += v[u];
+    }
+    row_sums(acc, red, g.gZ + (int64_t)l * kD);
+}
+
 __global__ __launch_bounds__(kBlock) void mlp_grads_kernel(FusedGrads g) {
-    __shared__ float red[kBlock * kD];
+    __shared__ float red[kBlock];
     const int tid = threadIdx.x;
     const int64_t nS = g.Bp / kChunk;
     const int64_t nT = g.Bp / kTB;
@@ -439,15 +550,16 @@ __global__ __launch_bounds__(kBlock) void mlp_grads_kernel(FusedGrads g) {
     // dW2 partials: 16 tiles per chunk
     if (job < 16 * nS) {
         const int64_t s = job / 16, t = job % 16;
-        grad_tile(g.dZ2rT, g.H1rT, g.Bp, 64 * (t / 4), 64 * (t % 4), s * kChunk,
-                  g.ws2 + s * (int64_t)kH * kH, kH);
+        grad_tile<kH, kH>(g.dZ2rT, g.H1rT, 64 * (t / 4), 64 * (t % 4), s * kChunk,
+                          g.ws2 + s * (int64_t)kH * kH, kH);
         return;
     }
     job -= 16 * nS;
     // dW1 partials: 4 tiles per chunk
     if (job < 4 * nS) {
         const int64_t s = job / 4, t = job % 4;
-        grad_tile(g.dZ1rT, g.XrT, g.Bp, 64 * t, 0, s * kChunk, g.ws1 + s * (int64_t)kH * kD2, kD2);
+        grad_tile<kH, kD2>(g.dZ1rT, g.XrT, 64 * t, 0, s * kChunk,
+                           g.ws1 + s * (int64_t)kH * kD2, kD2);
         return;
     }
     job -= 4 * nS;
@@ -483,74 +595,11 @@ __global__ __launch_bounds__(kBlock) void mlp_grads_kernel(FusedGrads g) {
     }
     job -= 1;
     if (job < g.M) {
-        // embedding tables of column j: one occurrence per thread at a time
-        // (occurrences in candidate-then-series order), then fixed-order sums
-        const int32_t j = (int32_t)job;
-        float ge[kD], gf[kD], gt[kD];
-#pragma unroll
-        for (int c = 0; c < kD; ++c) ge[c] = gf[c] = gt[c] = 0.f;
-        const int32_t o1 = g.occ_start[j + 1];
-        for (int32_t o = g.occ_start[j] + tid; o < o1; o += kBlock) {
-            const int32_t pos = g.occ_pos[o], b = g.occ_b[o];
-            const int32_t s = g.off[b], e = g.off[b + 1];
-            const float4 *dx = reinterpret_cast<const float4 *>(g.dX + (int64_t)b * kD2);
-            const float inv_l = 1.f / (float)(e - s);
-#pragma unroll
-            for (int q = 0; q < kD / 4; ++q) {
-                const float4 x = dx[q];
-                ge[4 * q] += x.x * inv_l;
-                ge[4 * q + 1] += x.y * inv_l;
-                ge[4 * q + 2] += x.z * inv_l;
-                ge[4 * q + 3] += x.w * inv_l;
-            }
-            if (e - s > 1) {
-                const float inv = 1.f / (float)(e - s - 1);
-                const bool has_next = pos + 1 < e, has_prev = pos > s;
-                const float4 *tn = reinterpret_cast<const float4 *>(
-                    g.T + (int64_t)g.cols[has_next ? pos + 1 : pos] * kD);
-                const float4 *fp = reinterpret_cast<const float4 *>(
-                    g.F + (int64_t)g.cols[has_prev ? pos - 1 : pos] * kD);
-#pragma unroll
-                for (int q = 0; q < kD / 4; ++q) {
-                    const float4 x = dx[kD / 4 + q];
-                    const float xs[4] = {x.x, x.y, x.z, x.w};
-                    const float4 tv = tn[q], fv = fp[q];
-                    const float ts[4] = {tv.x, tv.y, tv.z, tv.w};
-                    const float fs[4] = {fv.x, fv.y, fv.z, fv.w};
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        if (has_next) gf[4 * q + u] += xs[u] * ts[u] * inv;
-                        if (has_prev) gt[4 * q + u] += xs[u] * fs[u] * inv;
-                    }
-                }
-            }
-        }
-        block_sum(ge, red, g.gE + (int64_t)j * kD);
-        block_sum(gf, red, g.gF + (int64_t)j * kD);
-        block_sum(gt, red, g.gT + (int64_t)j * kD);
+        column_grads(g, (int32_t)job, red);
         return;
     }
     job -= g.M;
-    if (job <= g.M) {
-        // length embedding: candidates of length l, one per thread at a time
-        const int32_t l = (int32_t)job;
-        float gz[kD];
-#pragma unroll
-        for (int c = 0; c < kD; ++c) gz[c] = 0.f;
-        const int32_t o1 = g.len_start[l + 1];
-        for (int32_t o = g.len_start[l] + tid; o < o1; o += kBlock) {
-            const float4 *dx = reinterpret_cast<const float4 *>(g.dX + (int64_t)g.len_b[o] * kD2);
-#pragma unroll
-            for (int q = 0; q < kD / 4; ++q) {
-                const float4 x = dx[q];
-                gz[4 * q] += x.x;
-                gz[4 * q + 1] += x.y;
-                gz[4 * q + 2] += x.z;
-                gz[4 * q + 3] += x.w;
-            }
-        }
-        block_sum(gz, red, g.gZ + (int64_t)l * kD);
-    }
+    if (job <= g.M) length_grads(g, (int32_t)job, red);
 }
 
 // ------------------------------------------------------------- kernel C --
@@ -606,7 +655,7 @@ int32_t fused_tile_rows() { return kTB; }
 int32_t fused_chunk() { return kChunk; }
 
 hipError_t fused_rows(const FusedRows &a, hipStream_t s) {
-    hipLaunchKernelGGL(mlp_rows_kernel, dim3((unsigned)(a.Bp / kTB)), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(mlp_rows_kernel, dim3((unsigned)(a.Bp / kTB)), dim3(kRowsBlock), 0, s, a);
     return hipGetLastError();
 }
 
