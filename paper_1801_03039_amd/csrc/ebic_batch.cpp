@@ -18,6 +18,7 @@
 #include <atomic>
 #include <chrono>
 #include <climits>
+#include <cstring>
 #include <memory>
 #include <mutex>
 #include <string>
@@ -72,6 +73,8 @@ namespace {
 // threads once they hold kPackParallelCols columns or more.
 constexpr int32_t kPackThreads = 8;
 constexpr int64_t kPackParallelCols = int64_t(1) << 17;
+// ... or this many if they are only packed.
+constexpr int64_t kPackOnlyParallelCols = int64_t(1) << 21;
 
 ebic_status bfail(ebic_status st, const std::string &msg) {
     set_thread_error(msg.c_str());
@@ -129,6 +132,7 @@ struct Request {
     int64_t n_cand = 0, n_cols = 0;
     const ebic_params *params = nullptr;
     bool masks = false;
+    bool mark_repeats = false;   // series that repeat a column get count -1
 };
 
 // Capacity for n candidates / n column entries / mask words.
@@ -360,6 +364,8 @@ ebic_status run_request(ebic_batch *b, const Request &q, int32_t workgroups, int
         if (q.masks) maskw += (int64_t)P * 2 * c->W;
     }
     BHIP(hipEventRecord(b->ev1, b->stream));
+    if (q.mark_repeats)
+        BHIP(launch_mark_repeats(b->d_off, b->d_cols, (int32_t)q.n_cand, b->d_counts, b->stream));
     if (copy_back) {
         BHIP(hipMemcpyAsync(b->h_counts, b->d_counts, sizeof(int32_t) * (size_t)q.n_cand,
                             hipMemcpyDeviceToHost, b->stream));
@@ -668,6 +674,7 @@ ebic_status ebic_batch_evaluate(ebic_batch *b, const int32_t *const *offsets,
     q.P.assign((size_t)R, 0);
     std::vector<int64_t> cand_base((size_t)R, 0), col_base((size_t)R, 0);
     int64_t n_cols = 0, n_mask = 0;
+    int32_t longest = 0;
     // Pass 1: counts, pointers and offsets (which size the staging buffers).
     for (int32_t r = 0; r < R; ++r) {
         if (P[r] < 0) return bfail(EBIC_E_ARG, "P must be >= 0");
@@ -676,13 +683,11 @@ ebic_status ebic_batch_evaluate(ebic_batch *b, const int32_t *const *offsets,
         if (!offsets[r] || !cols[r] || !counts[r] || !fitness[r] || (q.masks && !masks[r]))
             return bfail(EBIC_E_ARG, "null per-run array");
         const int32_t *o = offsets[r];
-        if (o[0] != 0)
-            return bfail(EBIC_E_ARG, "run " + std::to_string(r) + ": offsets[0] must be 0");
-        for (int32_t i = 0; i < P[r]; ++i)
-            if (o[i + 1] <= o[i])
-                return bfail(EBIC_E_ARG, "run " + std::to_string(r) +
-                                             ": offsets must increase (every series has L >= 1); "
-                                             "candidate " + std::to_string(i));
+        ebic_status ost = EBIC_OK;
+        int32_t run_longest = 0;
+        if (!valid_offsets(c, o, P[r], &run_longest, &ost))
+            return bfail(ost, "run " + std::to_string(r) + ": " + c->err);
+        longest = std::max(longest, run_longest);
         if ((int64_t)P[r] * c->W > (int64_t(1) << 32) - 256)
             return bfail(EBIC_E_ARG, "population too large for one launch");
         q.P[(size_t)r] = P[r];
@@ -699,33 +704,54 @@ ebic_status ebic_batch_evaluate(ebic_batch *b, const int32_t *const *offsets,
     BHIP(hipSetDevice(b->device));
     ebic_status st = reserve(b, q.n_cand, n_cols, n_mask);
     if (st != EBIC_OK) return st;
-    // Pass 2: every run's columns checked (range, distinct within a series)
-    // and packed into the staging buffers in one pass, runs spread over host
-    // threads when there is enough to share; the first failing run (in run
-    // order) is reported.
+    // Pass 2: every run's columns packed into the staging buffers, and
+    // checked (range, distinct within a series): after the launch on the
+    // device when there are many (ebic_evaluate's rule), else here in the
+    // same pass.  Runs are spread over host threads when there is enough to
+    // share; the first failing run (in run order) is reported.
+    const bool check_after = !q.masks && !tune_now && n_cols >= kDeviceCheckEntries &&
+                             longest <= kDeviceCheckMaxLen;
     std::vector<ebic_status> run_st((size_t)R, EBIC_OK);
     auto pack = [&](int32_t r) {
         if (!q.P[(size_t)r]) return;
+        int32_t *off = b->h_off + cand_base[(size_t)r], *c = b->h_cols + col_base[(size_t)r];
+        if (check_after) {
+            for (int32_t i = 0; i < q.P[(size_t)r]; ++i)
+                off[i] = (int32_t)col_base[(size_t)r] + offsets[r][i];
+            std::memcpy(c, cols[r], sizeof(int32_t) * (size_t)offsets[r][q.P[(size_t)r]]);
+            return;
+        }
         ebic_status s = EBIC_OK;
         if (!pack_valid_cbf(b->ctx[(size_t)r], offsets[r], cols[r], q.P[(size_t)r],
-                            (int32_t)col_base[(size_t)r], b->h_off + cand_base[(size_t)r],
-                            b->h_cols + col_base[(size_t)r], &s))
+                            (int32_t)col_base[(size_t)r], off, c, &s))
             run_st[(size_t)r] = s;
     };
     const int32_t threads =
-        n_cols < kPackParallelCols
+        n_cols < (check_after ? kPackOnlyParallelCols : kPackParallelCols)
             ? 1
             : std::min<int32_t>({R, kPackThreads,
                                  (int32_t)std::max(1u, std::thread::hardware_concurrency())});
     parallel_for(R, threads, pack);
-    for (int32_t r = 0; r < R; ++r)
-        if (run_st[(size_t)r] != EBIC_OK) {
-            set_thread_error(("run " + std::to_string(r) + ": " + b->ctx[(size_t)r]->err).c_str());
-            return run_st[(size_t)r];
-        }
+    auto refused = [&]() -> ebic_status {
+        for (int32_t r = 0; r < R; ++r)
+            if (run_st[(size_t)r] != EBIC_OK) {
+                set_thread_error(("run " + std::to_string(r) + ": " + b->ctx[(size_t)r]->err).c_str());
+                return run_st[(size_t)r];
+            }
+        return EBIC_OK;
+    };
+    if ((st = refused()) != EBIC_OK) return st;
     b->h_off[q.n_cand] = (int32_t)n_cols;
     if (tune_now && (st = tune(b, q)) != EBIC_OK) return st;
+    q.mark_repeats = check_after;
     if ((st = run_request(b, q, b->workgroups, b->unroll, b->words, b->whole)) != EBIC_OK) return st;
+    if (check_after && any_negative(b->h_counts, q.n_cand)) {
+        for (int32_t r = 0; r < R; ++r)
+            if (q.P[(size_t)r] && any_negative(b->h_counts + cand_base[(size_t)r], q.P[(size_t)r]))
+                (void)valid_cbf(b->ctx[(size_t)r], offsets[r], cols[r], q.P[(size_t)r],
+                                &run_st[(size_t)r]);
+        if ((st = refused()) != EBIC_OK) return st;
+    }
     int64_t cand = 0, mw = 0;
     for (int32_t r = 0; r < R; ++r) {
         const int32_t n = q.P[(size_t)r];

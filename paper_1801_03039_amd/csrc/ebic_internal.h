@@ -187,11 +187,29 @@ ebic_status fail_status(ebic_ctx *ctx, ebic_status st, const char *msg);
 // (ebic_noalloc.hip); called with `device` current.
 hipError_t noalloc_setup(int device);
 
+// counts[c] = -1 for every series of the CBF (offsets checked) that repeats a
+// column (ebic_check.hip).  With the count -1 that the evaluators give to a
+// series with a column outside the matrix, every refused series of a host
+// population has a negative count after it.
+hipError_t launch_mark_repeats(const int32_t *offsets, const int32_t *cols, int32_t P,
+                               int32_t *counts, hipStream_t stream);
+// Host populations from this many column entries on are checked on the
+// device; a launch costs as much as the check of about this many columns on
+// the host.  Series longer than kDeviceCheckMaxLen are compared all pairs on
+// the device, so their populations stay with the host.
+constexpr int64_t kDeviceCheckEntries = 4096;
+constexpr int32_t kDeviceCheckMaxLen = 512;
+
 // Runtime helpers shared with the multi-run driver (ebic_runtime.cpp).
 void set_thread_error(const char *msg);
 ebic_status ensure_index(ebic_ctx *ctx);  // builds the order index if missing
 bool valid_cbf(ebic_ctx *ctx, const int32_t *offsets, const int32_t *cols, int32_t P,
                ebic_status *st);          // host CBF checks of ebic_evaluate
+// Whether one of n counts is negative.
+bool any_negative(const int32_t *counts, int64_t n);
+// The offsets' share of those checks, and the longest series.
+bool valid_offsets(ebic_ctx *ctx, const int32_t *offsets, int32_t P, int32_t *longest,
+                   ebic_status *st);
 // The same checks, copying the columns to dst_cols (column i of the CBF to
 // dst_cols[i]) and dst_off[c] = col_base + offsets[c] for c < P in one pass.
 bool pack_valid_cbf(ebic_ctx *ctx, const int32_t *offsets, const int32_t *cols, int32_t P,

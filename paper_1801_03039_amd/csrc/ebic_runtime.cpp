@@ -325,6 +325,29 @@ ebic_status create_common(const float *a, bool on_device, int64_t n_rows, int32_
     return EBIC_OK;
 }
 
+// offsets[0] = 0 and increasing; *longest the longest series.
+bool check_offsets(ebic_ctx *ctx, const int32_t *offsets, int32_t P, int32_t *longest,
+                   ebic_status *st) {
+    if (offsets[0] != 0) {
+        *st = fail(ctx, EBIC_E_ARG, "offsets[0] must be 0");
+        return false;
+    }
+    int32_t most = 0;
+    bool wrong = false;
+    for (int32_t c = 0; c < P; ++c) {
+        wrong |= offsets[c + 1] <= offsets[c];
+        const int32_t len = (int32_t)((uint32_t)offsets[c + 1] - (uint32_t)offsets[c]);
+        most = len > most ? len : most;
+    }
+    *longest = most;
+    if (!wrong) return true;
+    int32_t c = 0;
+    while (offsets[c + 1] > offsets[c]) ++c;
+    *st = fail(ctx, EBIC_E_ARG,
+               "offsets must increase (every series has L >= 1); candidate " + std::to_string(c));
+    return false;
+}
+
 // Host CBF checks: offsets[0] = 0, increasing offsets, columns in range and
 // distinct within a series.  With dst_cols, the columns are also copied to
 // dst_cols and dst_off[c] = col_base + offsets[c] for c < P, in the same pass.
@@ -414,6 +437,15 @@ bool valid_cbf(ebic_ctx *ctx, const int32_t *offsets, const int32_t *cols, int32
                ebic_status *st) {
     return check_cbf(ctx, offsets, cols, P, st);
 }
+bool any_negative(const int32_t *counts, int64_t n) {
+    int32_t all = 0;
+    for (int64_t i = 0; i < n; ++i) all |= counts[i];
+    return all < 0;
+}
+bool valid_offsets(ebic_ctx *ctx, const int32_t *offsets, int32_t P, int32_t *longest,
+                   ebic_status *st) {
+    return check_offsets(ctx, offsets, P, longest, st);
+}
 bool pack_valid_cbf(ebic_ctx *ctx, const int32_t *offsets, const int32_t *cols, int32_t P,
                     int32_t col_base, int32_t *dst_off, int32_t *dst_cols, ebic_status *st) {
     return check_cbf(ctx, offsets, cols, P, st, dst_off, dst_cols, col_base);
@@ -501,7 +533,17 @@ ebic_status ebic_evaluate(ebic_ctx *ctx, const int32_t *offsets, const int32_t *
     if (!offsets || !cols || !counts || !fitness)
         return fail(ctx, EBIC_E_ARG, "null pointer");
     if (params->want_masks && !masks) return fail(ctx, EBIC_E_ARG, "want_masks needs masks");
-    if (!check_cbf(ctx, offsets, cols, P, &st)) return st;
+    // The offsets are checked here.  Columns out of range and repeated ones
+    // are refused after the launch when there are many: the evaluators read
+    // nothing outside the index and mark such candidates, a second kernel
+    // marks repeats, and the host only looks for a mark.  (The first wrong
+    // offset and the first wrong column are reported in candidate order, and
+    // results with masks go straight to the caller: those calls check first.)
+    int32_t longest = 0;
+    const bool offsets_ok = check_offsets(ctx, offsets, P, &longest, &st);
+    const bool check_after = offsets_ok && !params->want_masks &&
+                             offsets[P] >= kDeviceCheckEntries && longest <= kDeviceCheckMaxLen;
+    if (!check_after && !check_cbf(ctx, offsets, cols, P, &st)) return st;
     const int64_t n_entries = offsets[P];
     // One upload (offsets then columns) and one download (fitness then
     // counts), both through pinned staging buffers.
@@ -530,6 +572,7 @@ ebic_status ebic_evaluate(ebic_ctx *ctx, const int32_t *offsets, const int32_t *
                mask_words ? ctx->d_masks : nullptr, d_counts, ctx->d_res, ctx->d_log,
                ctx->d_acc};
     if ((st = launch_all(ctx, e, use_index, s)) != EBIC_OK) return st;
+    if (check_after) HIP_TRY(ctx, launch_mark_repeats(e.offsets, e.cols, P, d_counts, s));
     HIP_TRY(ctx, hipMemcpyAsync(ctx->h_res, ctx->d_res,
                                 sizeof(double) * (size_t)P + sizeof(int32_t) * (size_t)P,
                                 hipMemcpyDeviceToHost, s));
@@ -537,8 +580,11 @@ ebic_status ebic_evaluate(ebic_ctx *ctx, const int32_t *offsets, const int32_t *
         HIP_TRY(ctx, hipMemcpyAsync(masks, ctx->d_masks, sizeof(uint64_t) * (size_t)mask_words,
                                     hipMemcpyDeviceToHost, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
+    const int32_t *h_counts = reinterpret_cast<const int32_t *>(ctx->h_res + P);
+    if (check_after && any_negative(h_counts, P) && !check_cbf(ctx, offsets, cols, P, &st))
+        return st;
     std::memcpy(fitness, ctx->h_res, sizeof(double) * (size_t)P);
-    std::memcpy(counts, ctx->h_res + P, sizeof(int32_t) * (size_t)P);
+    std::memcpy(counts, h_counts, sizeof(int32_t) * (size_t)P);
     return EBIC_OK;
 }
 
