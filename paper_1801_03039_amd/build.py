@@ -26,7 +26,7 @@ ARCH = "gfx950"
 SOURCES = ["ebic_kernels.hip", "ebic_tolerance.hip", "ebic_index.hip", "ebic_batch_kernels.hip", "ebic_runtime.cpp", "ebic_evolve.cpp", "ebic_batch.cpp",
            "ebic_mlp_kernels.hip", "ebic_mlp.cpp", "ebic_surrogate.cpp", "ebic_scores.hip",
            "ebic_checkpoint.cpp", "ebic_noalloc.hip", "ebic_check.hip", "ebic_steps.hip",
-           "ebic_mlp_fused.hip"]
+           "ebic_mlp_fused.hip", "ebic_mlp_lists.hip"]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math", "-Wall",
           "-I", INCLUDE, "-I", CSRC]

@@ -30,7 +30,17 @@ struct ebic_mlp {
     uint16_t *W1b = nullptr, *W2b = nullptr, *w3b = nullptr;
     int64_t step = 0;
     int32_t last_B = 0;   // batch of the last training call (its loss is in sq)
-    // per-batch buffers (capacity cap_B candidates, cap_L column entries)
+    // The batch as one copy brings it (`in`: offsets, columns, targets; off,
+    // cols and t point into it), the pinned room that stages it and takes the
+    // results, and the event after the last copy out of that.
+    int32_t *in = nullptr, *h_io = nullptr;
+    int64_t cap_in = 0, cap_io = 0;
+    hipEvent_t copied = nullptr;
+    bool copying = false;
+    // list workspace, and per-batch buffers (capacity cap_B candidates, cap_L
+    // column entries)
+    int32_t *lists_ws = nullptr;
+    int64_t cap_lists = 0;
     int64_t cap_B = 0, cap_L = 0;
     int32_t *off = nullptr, *cols = nullptr, *occ_start = nullptr, *occ_pos = nullptr,
             *occ_b = nullptr, *len_start = nullptr, *len_b = nullptr;
@@ -76,41 +86,41 @@ hipError_t dalloc(T *&p, int64_t n) {
     return hipMalloc((void **)&p, sizeof(T) * (size_t)std::max<int64_t>(n, 1));
 }
 
+// Buffers of a batch of B candidates, and its lists of L entries (0: none).
 ebic_status reserve(ebic_mlp *m, int64_t B, int64_t L) {
     const int64_t H = m->H, D = m->D;
     if (B > m->cap_B) {
         MHIP(hipStreamSynchronize(m->stream));
         const int64_t c = std::max<int64_t>(B, m->cap_B * 2);
-        MHIP(dalloc(m->off, c + 1));
-        MHIP(dalloc(m->X, c * 2 * D));
-        MHIP(dalloc(m->Xb, c * 2 * D));
-        MHIP(dalloc(m->Z1, c * H));
-        MHIP(dalloc(m->H1b, c * H));
-        MHIP(dalloc(m->Z2, c * H));
-        MHIP(dalloc(m->H2b, c * H));
         MHIP(dalloc(m->y, c));
-        MHIP(dalloc(m->t, c));
-        MHIP(dalloc(m->dy, c));
         MHIP(dalloc(m->sq, c));
-        MHIP(dalloc(m->dZ2, c * H));
-        MHIP(dalloc(m->dZ2b, c * H));
-        MHIP(dalloc(m->G1, c * H));
-        MHIP(dalloc(m->dZ1, c * H));
-        MHIP(dalloc(m->dZ1b, c * H));
-        MHIP(dalloc(m->dX, c * 2 * D));
         MHIP(dalloc(m->len_b, c));
+        if (!m->fused) {   // (the fused step has its own)
+            MHIP(dalloc(m->X, c * 2 * D));
+            MHIP(dalloc(m->Xb, c * 2 * D));
+            MHIP(dalloc(m->Z1, c * H));
+            MHIP(dalloc(m->H1b, c * H));
+            MHIP(dalloc(m->Z2, c * H));
+            MHIP(dalloc(m->H2b, c * H));
+            MHIP(dalloc(m->dy, c));
+            MHIP(dalloc(m->dZ2, c * H));
+            MHIP(dalloc(m->dZ2b, c * H));
+            MHIP(dalloc(m->G1, c * H));
+            MHIP(dalloc(m->dZ1, c * H));
+            MHIP(dalloc(m->dZ1b, c * H));
+            MHIP(dalloc(m->dX, c * 2 * D));
+        }
         m->cap_B = c;
     }
     if (L > m->cap_L) {
         MHIP(hipStreamSynchronize(m->stream));
         const int64_t c = std::max<int64_t>(L, m->cap_L * 2);
-        MHIP(dalloc(m->cols, c));
         MHIP(dalloc(m->occ_pos, c));
         MHIP(dalloc(m->occ_b, c));
         m->cap_L = c;
     }
     const int64_t need_ws = (int64_t)kMaxSplits * std::max<int64_t>(H * H, H * 2 * D);
-    if (need_ws > m->cap_ws) {
+    if (!m->fused && need_ws > m->cap_ws) {
         MHIP(dalloc(m->ws, need_ws));
         m->cap_ws = need_ws;
     }
@@ -251,70 +261,125 @@ ebic_status fused_step(ebic_mlp *m, int32_t B, int32_t mode, float c1, float c2)
     return EBIC_OK;
 }
 
+// (branch-free passes, so that the compiler vectorises them)
 bool check_cbf(const ebic_mlp *m, const int32_t *off, const int32_t *cols, int32_t B) {
     if (off[0] != 0) return false;
+    const int32_t M = m->M;
+    bool wrong = false;
     for (int32_t b = 0; b < B; ++b) {
-        if (off[b + 1] <= off[b] || off[b + 1] - off[b] > m->M) return false;
-        for (int32_t i = off[b]; i < off[b + 1]; ++i)
-            if (cols[i] < 0 || cols[i] >= m->M) return false;
+        wrong |= off[b + 1] <= off[b];
+        wrong |= (int64_t)off[b + 1] - off[b] > M;
     }
-    return true;
+    if (wrong) return false;
+    const int64_t L = off[B];
+    for (int64_t i = 0; i < L; ++i) wrong |= (cols[i] < 0) | (cols[i] >= M);
+    return !wrong;
 }
 
-// Uploads a batch (CBF, occurrence lists by column, optional targets).
+// Pinned host room for n words (grown by at least a factor of two), of which
+// nothing is in use.
+hipError_t reserve_io(ebic_mlp *m, int64_t n) {
+    if (n <= m->cap_io) return hipSuccess;
+    const int64_t c = std::max<int64_t>(n, m->cap_io * 2);
+    if (m->h_io) {
+        hipError_t e = hipHostFree(m->h_io);
+        m->h_io = nullptr;
+        m->cap_io = 0;
+        if (e != hipSuccess) return e;
+    }
+    hipError_t e = hipHostMalloc((void **)&m->h_io, sizeof(int32_t) * (size_t)c,
+                                 hipHostMallocDefault);
+    if (e == hipSuccess) m->cap_io = c;
+    return e;
+}
+
+// The lists by column and by length on the host, for networks too wide for
+// the device's counters.
+ebic_status host_lists(ebic_mlp *m, const int32_t *off, const int32_t *cols, int32_t B) {
+    const int64_t L = off[B];
+    // CSR by column: every occurrence (position in cols, and its
+    // candidate) of column j, in candidate-then-series order.
+    std::vector<int32_t> start((size_t)m->M + 1, 0), pos((size_t)L), occ((size_t)L);
+    for (int64_t i = 0; i < L; ++i) ++start[(size_t)cols[i] + 1];
+    for (int32_t j = 0; j < m->M; ++j) start[(size_t)j + 1] += start[(size_t)j];
+    std::vector<int32_t> fill(start.begin(), start.end() - 1);
+    for (int32_t b = 0; b < B; ++b)
+        for (int32_t i = off[b]; i < off[b + 1]; ++i) {
+            const int32_t k = fill[(size_t)cols[i]]++;
+            pos[(size_t)k] = i;
+            occ[(size_t)k] = b;
+        }
+    // CSR by series length: the candidates of length l, in order.
+    std::vector<int32_t> lstart((size_t)m->M + 2, 0), lb((size_t)B);
+    for (int32_t b = 0; b < B; ++b) ++lstart[(size_t)(off[b + 1] - off[b]) + 1];
+    for (int32_t l = 0; l <= m->M; ++l) lstart[(size_t)l + 1] += lstart[(size_t)l];
+    std::vector<int32_t> lfill(lstart.begin(), lstart.end() - 1);
+    for (int32_t b = 0; b < B; ++b) lb[(size_t)lfill[(size_t)(off[b + 1] - off[b])]++] = b;
+    MHIP(hipStreamSynchronize(m->stream));  // no kernel still reads the previous lists
+    MHIP(hipMemcpy(m->occ_start, start.data(), sizeof(int32_t) * start.size(),
+                   hipMemcpyHostToDevice));
+    MHIP(hipMemcpy(m->occ_pos, pos.data(), sizeof(int32_t) * (size_t)L, hipMemcpyHostToDevice));
+    MHIP(hipMemcpy(m->occ_b, occ.data(), sizeof(int32_t) * (size_t)L, hipMemcpyHostToDevice));
+    MHIP(hipMemcpy(m->len_start, lstart.data(), sizeof(int32_t) * lstart.size(),
+                   hipMemcpyHostToDevice));
+    MHIP(hipMemcpy(m->len_b, lb.data(), sizeof(int32_t) * (size_t)B, hipMemcpyHostToDevice));
+    return EBIC_OK;
+}
+
+// Uploads a batch (CBF and optional targets, one copy through pinned memory)
+// and, with `occurrences`, builds its lists; the call will fetch `results`
+// words.
 ebic_status upload(ebic_mlp *m, const int32_t *off, const int32_t *cols, int32_t B,
-                   const float *target, bool occurrences) {
+                   const float *target, bool occurrences, int64_t results) {
     if (!off || !cols || B < 1) return mfail(EBIC_E_ARG, "need a non-empty CBF batch");
     if (!check_cbf(m, off, cols, B)) return mfail(EBIC_E_RANGE, "malformed CBF, a series longer than n_cols or a column out of range");
     const int64_t L = off[B];
-    ebic_status st = reserve(m, B, L);
+    ebic_status st = reserve(m, B, occurrences ? L : 0);
     if (st != EBIC_OK) return st;
-    MHIP(hipMemcpyAsync(m->off, off, sizeof(int32_t) * ((size_t)B + 1), hipMemcpyHostToDevice,
-                        m->stream));
-    MHIP(hipMemcpyAsync(m->cols, cols, sizeof(int32_t) * (size_t)L, hipMemcpyHostToDevice,
-                        m->stream));
-    if (target)
-        MHIP(hipMemcpyAsync(m->t, target, sizeof(float) * (size_t)B, hipMemcpyHostToDevice,
-                            m->stream));
-    if (occurrences) {
-        // CSR by column: every occurrence (position in cols, and its
-        // candidate) of column j, in candidate-then-series order.
-        std::vector<int32_t> start((size_t)m->M + 1, 0), pos((size_t)L), occ((size_t)L);
-        for (int64_t i = 0; i < L; ++i) ++start[(size_t)cols[i] + 1];
-        for (int32_t j = 0; j < m->M; ++j) start[(size_t)j + 1] += start[(size_t)j];
-        std::vector<int32_t> fill(start.begin(), start.end() - 1);
-        for (int32_t b = 0; b < B; ++b)
-            for (int32_t i = off[b]; i < off[b + 1]; ++i) {
-                const int32_t k = fill[(size_t)cols[i]]++;
-                pos[(size_t)k] = i;
-                occ[(size_t)k] = b;
-            }
-        // CSR by series length: the candidates of length l, in order.
-        std::vector<int32_t> lstart((size_t)m->M + 2, 0), lb((size_t)B);
-        for (int32_t b = 0; b < B; ++b) ++lstart[(size_t)(off[b + 1] - off[b]) + 1];
-        for (int32_t l = 0; l <= m->M; ++l) lstart[(size_t)l + 1] += lstart[(size_t)l];
-        std::vector<int32_t> lfill(lstart.begin(), lstart.end() - 1);
-        for (int32_t b = 0; b < B; ++b) lb[(size_t)lfill[(size_t)(off[b + 1] - off[b])]++] = b;
-        if (!m->occ_start) MHIP(hipMalloc((void **)&m->occ_start, sizeof(int32_t) * ((size_t)m->M + 1)));
-        if (!m->len_start) MHIP(hipMalloc((void **)&m->len_start, sizeof(int32_t) * ((size_t)m->M + 2)));
-        MHIP(hipStreamSynchronize(m->stream));  // no kernel still reads the previous lists
-        MHIP(hipMemcpy(m->occ_start, start.data(), sizeof(int32_t) * start.size(),
-                       hipMemcpyHostToDevice));
-        MHIP(hipMemcpy(m->occ_pos, pos.data(), sizeof(int32_t) * (size_t)L, hipMemcpyHostToDevice));
-        MHIP(hipMemcpy(m->occ_b, occ.data(), sizeof(int32_t) * (size_t)L, hipMemcpyHostToDevice));
-        MHIP(hipMemcpy(m->len_start, lstart.data(), sizeof(int32_t) * lstart.size(),
-                       hipMemcpyHostToDevice));
-        MHIP(hipMemcpy(m->len_b, lb.data(), sizeof(int32_t) * (size_t)B, hipMemcpyHostToDevice));
+    const int64_t n = (int64_t)B + 1 + L + (target ? B : 0);
+    if (m->copying) {   // the staging buffer's last copy (long done: kernels follow it)
+        MHIP(hipEventSynchronize(m->copied));
+        m->copying = false;
     }
+    MHIP(reserve_io(m, std::max(n, results)));
+    if (n > m->cap_in) {
+        MHIP(hipStreamSynchronize(m->stream));
+        const int64_t c = std::max<int64_t>(n, m->cap_in * 2);
+        m->cap_in = 0;
+        MHIP(dalloc(m->in, c));
+        m->cap_in = c;
+    }
+    m->off = m->in;
+    m->cols = m->in + B + 1;
+    m->t = reinterpret_cast<float *>(m->in + B + 1 + L);
+    std::memcpy(m->h_io, off, sizeof(int32_t) * ((size_t)B + 1));
+    std::memcpy(m->h_io + B + 1, cols, sizeof(int32_t) * (size_t)L);
+    if (target) std::memcpy(m->h_io + B + 1 + L, target, sizeof(float) * (size_t)B);
+    MHIP(hipMemcpyAsync(m->in, m->h_io, sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice,
+                        m->stream));
+    MHIP(hipEventRecord(m->copied, m->stream));
+    m->copying = true;
+    if (!occurrences) return EBIC_OK;
+    if (!m->occ_start) MHIP(hipMalloc((void **)&m->occ_start, sizeof(int32_t) * ((size_t)m->M + 1)));
+    if (!m->len_start) MHIP(hipMalloc((void **)&m->len_start, sizeof(int32_t) * ((size_t)m->M + 2)));
+    if (!mlp::lists_on_device(m->M)) return host_lists(m, off, cols, B);
+    const int64_t ws = mlp::lists_workspace(B, L, m->M);
+    if (ws > m->cap_lists) {
+        MHIP(hipStreamSynchronize(m->stream));
+        const int64_t c = std::max<int64_t>(ws, m->cap_lists * 2);
+        m->cap_lists = 0;
+        MHIP(dalloc(m->lists_ws, c));
+        m->cap_lists = c;
+    }
+    MHIP(mlp::build_lists(m->off, m->cols, B, L, m->M, m->lists_ws, m->occ_start, m->occ_pos,
+                          m->occ_b, m->len_start, m->len_b, m->stream));
     return EBIC_OK;
 }
 
 ebic_status forward(ebic_mlp *m, int32_t B) {
     const int32_t D = m->D, H = m->H;
     hipStream_t s = m->stream;
-    if (m->fused) {
-        ebic_status st = reserve_fused(m, B);
-        if (st != EBIC_OK) return st;
+    if (m->fused) {   // (without targets it stores nothing but y)
         MHIP(mlp::fused_rows(fused_rows_args(m, B, false), s));
         return EBIC_OK;
     }
@@ -385,19 +450,33 @@ ebic_status refresh_bf16(ebic_mlp *m) {
     return EBIC_OK;
 }
 
-float host_loss(ebic_mlp *m, int32_t B, ebic_status *st) {
-    std::vector<float> sq((size_t)B);
-    hipError_t e = hipMemcpyAsync(sq.data(), m->sq, sizeof(float) * (size_t)B,
-                                  hipMemcpyDeviceToHost, m->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
-    if (e != hipSuccess) {
-        *st = mfail(EBIC_E_DEVICE, std::string("loss copy: ") + hipGetErrorString(e));
-        return 0.f;
-    }
+// Copies n floats (and, with n2, n2 more) into the pinned room and waits for
+// them; the copy out of it that may still be queued is before these.
+ebic_status fetch(ebic_mlp *m, const float *src, int64_t n, const float *src2 = nullptr,
+                  int64_t n2 = 0) {
+    if (n + n2 > m->cap_io) MHIP(hipStreamSynchronize(m->stream));
+    MHIP(reserve_io(m, n + n2));
+    MHIP(hipMemcpyAsync(m->h_io, src, sizeof(float) * (size_t)n, hipMemcpyDeviceToHost,
+                        m->stream));
+    if (n2)
+        MHIP(hipMemcpyAsync(m->h_io + n, src2, sizeof(float) * (size_t)n2, hipMemcpyDeviceToHost,
+                            m->stream));
+    MHIP(hipStreamSynchronize(m->stream));
+    return EBIC_OK;
+}
+
+const float *fetched(const ebic_mlp *m) { return reinterpret_cast<const float *>(m->h_io); }
+
+// The mean of B squared errors, added in order.
+float mean_loss(const float *sq, int32_t B) {
     double acc = 0.0;
-    for (float v : sq) acc += v;
-    *st = EBIC_OK;
+    for (int32_t b = 0; b < B; ++b) acc += sq[b];
     return (float)(acc / B);
+}
+
+float host_loss(ebic_mlp *m, int32_t B, ebic_status *st) {
+    *st = fetch(m, m->sq, B);
+    return *st == EBIC_OK ? mean_loss(fetched(m), B) : 0.f;
 }
 
 struct SplitMix {
@@ -460,6 +539,7 @@ ebic_status ebic_mlp_create(int32_t n_cols, const ebic_mlp_config *cfg, uint64_t
     };
     hipError_t e = hipSetDevice(device);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&m->stream, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&m->copied, hipEventDisableTiming);
     if (e == hipSuccess) e = dalloc(m->p, m->n_params);
     if (e == hipSuccess) e = dalloc(m->g, m->n_params);
     if (e == hipSuccess) e = dalloc(m->m1, m->n_params);
@@ -484,13 +564,15 @@ ebic_status ebic_mlp_destroy(ebic_mlp *m) {
     if (!m) return EBIC_OK;
     (void)hipSetDevice(m->device);
     if (m->stream) (void)hipStreamSynchronize(m->stream);
-    void *bufs[] = {m->p, m->g, m->m1, m->m2, m->W1b, m->W2b, m->w3b, m->off, m->cols,
-                    m->occ_start, m->occ_pos, m->occ_b, m->len_start, m->len_b, m->X, m->Z1, m->Z2, m->y, m->t, m->dy, m->sq,
+    void *bufs[] = {m->p, m->g, m->m1, m->m2, m->W1b, m->W2b, m->w3b, m->in, m->lists_ws,
+                    m->occ_start, m->occ_pos, m->occ_b, m->len_start, m->len_b, m->X, m->Z1, m->Z2, m->y, m->dy, m->sq,
                     m->dZ2, m->G1, m->dZ1, m->dX, m->Xb, m->H1b, m->H2b, m->dZ2b, m->dZ1b, m->ws,
                     m->W1bT, m->W2bT, m->XrT, m->H1rT, m->dZ2rT, m->dZ1rT, m->fdX, m->ws1,
                     m->ws2, m->pw3, m->pb2, m->pb1, m->pb3};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
+    if (m->h_io) (void)hipHostFree(m->h_io);
+    if (m->copied) (void)hipEventDestroy(m->copied);
     if (m->stream) (void)hipStreamDestroy(m->stream);
     delete m;
     return EBIC_OK;
@@ -524,11 +606,11 @@ ebic_status ebic_mlp_predict(ebic_mlp *m, const int32_t *offsets, const int32_t 
                              float *y) {
     if (!m || !y) return mfail(EBIC_E_ARG, "null argument");
     MHIP(hipSetDevice(m->device));
-    ebic_status st = upload(m, offsets, cols, B, nullptr, false);
+    ebic_status st = upload(m, offsets, cols, B, nullptr, false, B);
     if (st != EBIC_OK) return st;
     if ((st = forward(m, B)) != EBIC_OK) return st;
-    MHIP(hipMemcpyAsync(y, m->y, sizeof(float) * (size_t)B, hipMemcpyDeviceToHost, m->stream));
-    MHIP(hipStreamSynchronize(m->stream));
+    if ((st = fetch(m, m->y, B)) != EBIC_OK) return st;
+    std::memcpy(y, m->h_io, sizeof(float) * (size_t)B);
     return EBIC_OK;
 }
 
@@ -536,7 +618,7 @@ ebic_status ebic_mlp_gradients(ebic_mlp *m, const int32_t *offsets, const int32_
                                int32_t B, const float *target, float *grad, float *loss) {
     if (!m || !target || !grad) return mfail(EBIC_E_ARG, "null argument");
     MHIP(hipSetDevice(m->device));
-    ebic_status st = upload(m, offsets, cols, B, target, true);
+    ebic_status st = upload(m, offsets, cols, B, target, true, m->n_params + B);
     if (st != EBIC_OK) return st;
     if (m->fused) {
         if ((st = reserve_fused(m, B)) != EBIC_OK ||
@@ -545,11 +627,9 @@ ebic_status ebic_mlp_gradients(ebic_mlp *m, const int32_t *offsets, const int32_
     } else if ((st = forward(m, B)) != EBIC_OK || (st = backward(m, B)) != EBIC_OK) {
         return st;
     }
-    MHIP(hipMemcpyAsync(grad, m->g, sizeof(float) * (size_t)m->n_params, hipMemcpyDeviceToHost,
-                        m->stream));
-    const float l = host_loss(m, B, &st);
-    if (st != EBIC_OK) return st;
-    if (loss) *loss = l;
+    if ((st = fetch(m, m->g, m->n_params, m->sq, B)) != EBIC_OK) return st;
+    std::memcpy(grad, m->h_io, sizeof(float) * (size_t)m->n_params);
+    if (loss) *loss = mean_loss(fetched(m) + m->n_params, B);
     return EBIC_OK;
 }
 
@@ -558,7 +638,7 @@ ebic_status ebic_mlp_train(ebic_mlp *m, const int32_t *offsets, const int32_t *c
     if (!m || !target) return mfail(EBIC_E_ARG, "null argument");
     if (steps < 1) return mfail(EBIC_E_ARG, "steps must be >= 1");
     MHIP(hipSetDevice(m->device));
-    ebic_status st = upload(m, offsets, cols, B, target, true);
+    ebic_status st = upload(m, offsets, cols, B, target, true, B);
     if (st != EBIC_OK) return st;
     if (m->fused && (st = reserve_fused(m, B)) != EBIC_OK) return st;
     for (int32_t k = 0; k < steps; ++k) {

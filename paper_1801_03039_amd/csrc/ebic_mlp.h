@@ -61,6 +61,16 @@ hipError_t adam(float *p, const float *g, float *m1, float *m2, int64_t n, float
                 float beta2, float eps, float c1, float c2, hipStream_t s);
 hipError_t cast_bf16(const float *src, int64_t n, uint16_t *dst, hipStream_t s);
 
+// The batch's entries by column and its candidates by length (ebic_mlp_lists.hip):
+// CSR occ_start [M + 1], occ_pos / occ_b [L] and len_start [M + 2], len_b [B],
+// each list in batch order.  ws: lists_workspace(B, L, M) ints.  For networks
+// too wide for it (lists_on_device false) the host builds the lists.
+bool lists_on_device(int32_t M);
+int64_t lists_workspace(int64_t B, int64_t L, int32_t M);
+hipError_t build_lists(const int32_t *off, const int32_t *cols, int32_t B, int64_t L, int32_t M,
+                       int32_t *ws, int32_t *occ_start, int32_t *occ_pos, int32_t *occ_b,
+                       int32_t *len_start, int32_t *len_b, hipStream_t s);
+
 // ------------------------------------------------ fused step (D 32, H 256) --
 // (ebic_mlp_fused.hip) Three launches per training step: rows (forward and
 // per-candidate backward per tile of candidates), grads (weight and
