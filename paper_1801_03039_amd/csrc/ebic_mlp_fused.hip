@@ -439,7 +439,7 @@ __device__ void grad_tile(const uint16_t *A, const uint16_t *Bm, int64_t m0, int
 // its 96 sums in registers, 212 VGPRs and three reductions through LDS, whose
 // rows met in two banks, these jobs took most of the kernel's 34 us.)
 constexpr int kRows = kBlock / kD;     // 8
-constexpr int kPlaces = 8;            // places whose loads are in flight
+constexpr int kPlaces = 16;           // a column's places whose loads are in flight
 static_assert(kRows * kD == kBlock && kD == 32, "half-waves are rows");
 
 // The rows' sums acc of one dimension each -> out[0..kD).
@@ -454,90 +454,92 @@ __device__ void row_sums(float acc, float *red, float *out) {
     __syncthreads();
 }
 
-// Column j: dE from its occurrences' dx / L, dF and dT from the pairs it
-// begins and ends.
+// Column j: dE from its occurrences' dx / L, dF from the pairs it begins (times
+// T of the next column) or dT from those it ends (times F of the one before).
+// A job each, as a long list lasts as long as one compute unit's chain of
+// entries and gathered rows; 16 places at a time, so that the entries are read
+// twice.  The kernel takes 17.8 us at 8192 candidates over 500 columns (190
+// entries a list), 61 us over 20 columns (3000 a list); with the three in one
+// job, 8 places at a time, 18.1 and 103 us; with every place's sum kept over
+// the rounds (32, 165 VGPRs) 24.2 and 62 us.
+enum Table { kTabE, kTabF, kTabT };
+template <Table TAB>
 __device__ void column_grads(const FusedGrads &g, int32_t j, float *red) {
+    constexpr bool PAIRS = TAB != kTabE;
     const int r = threadIdx.x / kD, c = threadIdx.x % kD;
     const int32_t o0 = g.occ_start[j], o1 = g.occ_start[j + 1];
-    float ae = 0.f, af = 0.f, at = 0.f;
+    const float *const other = TAB == kTabF ? g.T : g.F;
+    const float *const dx = g.dX + (PAIRS ? kD : 0) + c;
+    float acc = 0.f;
     const int32_t row0 = o0 + r * kD;
-    // lane c: what the entry at place c of the row's round at `o` needs
-    int32_t b, next, prev;
-    float inv_l, inv;
+    // lane c: what the entry at place c of the row's round at `o` needs: its
+    // candidate, the pair's other column (-1: none) and the mean's factor
+    int32_t b, col;
+    float inv;
     auto entry = [&](int32_t o) {
         const int32_t mine = o + c < o1 ? o + c : o1 - 1;
-        const int32_t pos = g.occ_pos[mine];
         b = g.occ_b[mine];
         const int32_t s = g.off[b], e = g.off[b + 1], L = e - s;
-        next = pos + 1 < e ? g.cols[pos + 1] : -1;
-        prev = pos > s ? g.cols[pos - 1] : -1;
-        inv_l = 1.f / (float)L;
-        inv = L > 1 ? 1.f / (float)(L - 1) : 0.f;
+        if (PAIRS) {
+            const int32_t pos = g.occ_pos[mine] + (TAB == kTabF ? 1 : -1);
+            col = pos >= s && pos < e ? g.cols[pos] : -1;
+            inv = L > 1 ? 1.f / (float)(L - 1) : 0.f;
+        } else {
+            inv = 1.f / (float)L;
+        }
     };
     if (row0 < o1) entry(row0);
-    for (int p0 = 0; p0 < kD && row0 + p0 < o1; p0 += kPlaces) {
-        float ve[kPlaces], vf[kPlaces], vt[kPlaces];
-#pragma unroll
-        for (int u = 0; u < kPlaces; ++u) ve[u] = vf[u] = vt[u] = 0.f;
-        for (int32_t o = row0; o + p0 < o1; o += kBlock) {
-            if (o != row0 || (p0 > 0 && row0 + kBlock < o1)) entry(o);
-            float xe[kPlaces], xp[kPlaces], tn[kPlaces], fp[kPlaces];
-#pragma unroll
-            for (int u = 0; u < kPlaces; ++u) {
-                const int32_t bu = __shfl(b, p0 + u, kD);
-                const int32_t nu = __shfl(next, p0 + u, kD), pu = __shfl(prev, p0 + u, kD);
-                xe[u] = g.dX[(int64_t)bu * kD2 + c];
-                xp[u] = g.dX[(int64_t)bu * kD2 + kD + c];
-                tn[u] = g.T[(int64_t)(nu < 0 ? 0 : nu) * kD + c];
-                fp[u] = g.F[(int64_t)(pu < 0 ? 0 : pu) * kD + c];
-            }
-#pragma unroll
-            for (int u = 0; u < kPlaces; ++u) {
-                const float il = __shfl(inv_l, p0 + u, kD), iv = __shfl(inv, p0 + u, kD);
-                const bool has_next = __shfl(next, p0 + u, kD) >= 0;
-                const bool has_prev = __shfl(prev, p0 + u, kD) >= 0;
-                if (o + p0 + u < o1) {
-                    ve[u] += xe[u] * il;
-                    if (has_next) vf[u] += xp[u] * tn[u] * iv;
-                    if (has_prev) vt[u] += xp[u] * fp[u] * iv;
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kPlaces; ++u) {
-            ae += ve[u];
-            af += vf[u];
-            at += vt[u];
-        }
-    }
-    row_sums(ae, red, g.gE + (int64_t)j * kD);
-    row_sums(af, red, g.gF + (int64_t)j * kD);
-    row_sums(at, red, g.gT + (int64_t)j * kD);
-}
-
-// Length l: dZ from its candidates' dx.
-__device__ void length_grads(const FusedGrads &g, int32_t l, float *red) {
-    const int r = threadIdx.x / kD, c = threadIdx.x % kD;
-    const int32_t o0 = g.len_start[l], o1 = g.len_start[l + 1];
-    const int32_t row0 = o0 + r * kD;
-    float acc = 0.f;
     for (int p0 = 0; p0 < kD && row0 + p0 < o1; p0 += kPlaces) {
         float v[kPlaces];
 #pragma unroll
         for (int u = 0; u < kPlaces; ++u) v[u] = 0.f;
         for (int32_t o = row0; o + p0 < o1; o += kBlock) {
-            const int32_t b = g.len_b[o + c < o1 ? o + c : o1 - 1];   // lane c: place c
-            float x[kPlaces];
+            if (o != row0 || (p0 > 0 && row0 + kBlock < o1)) entry(o);
+            float x[kPlaces], w[kPlaces];
 #pragma unroll
-            for (int u = 0; u < kPlaces; ++u)
-                x[u] = g.dX[(int64_t)__shfl(b, p0 + u, kD) * kD2 + c];
+            for (int u = 0; u < kPlaces; ++u) {
+                x[u] = dx[(int64_t)__shfl(b, p0 + u, kD) * kD2];
+                if (PAIRS) {
+                    const int32_t cu = __shfl(col, p0 + u, kD);
+                    w[u] = other[(int64_t)(cu < 0 ? 0 : cu) * kD + c];
+                }
+            }
 #pragma unroll
-            for (int u = 0; u < kPlaces; ++u)
-                if (o + p0 + u < o1) v[u] += x[u];
+            for (int u = 0; u < kPlaces; ++u) {
+                const float iv = __shfl(inv, p0 + u, kD);
+                const bool have = !PAIRS || __shfl(col, p0 + u, kD) >= 0;
+                if (have && o + p0 + u < o1) v[u] += PAIRS ? x[u] * w[u] * iv : x[u] * iv;
+            }
         }
 #pragma unroll
         for (int u = 0; u < kPlaces; ++u) acc += v[u];
     }
+    float *const out = TAB == kTabE ? g.gE : (TAB == kTabF ? g.gF : g.gT);
+    row_sums(acc, red, out + (int64_t)j * kD);
+}
+
+// Length l: dZ from its candidates' dx; every place's sum stays in registers,
+// and the next round's candidates are read ahead (8192 candidates of one
+// length: 55 us, 85 with 8 places at a time).
+__device__ void length_grads(const FusedGrads &g, int32_t l, float *red) {
+    const int r = threadIdx.x / kD, c = threadIdx.x % kD;
+    const int32_t o0 = g.len_start[l], o1 = g.len_start[l + 1];
+    const int32_t row0 = o0 + r * kD;
+    float acc = 0.f, v[kD] = {};
+    auto owner = [&](int32_t o) { return g.len_b[o + c < o1 ? o + c : o1 - 1]; };
+    int32_t b = row0 < o1 ? owner(row0) : 0;   // lane c: place c
+    for (int32_t o = row0; o < o1; o += kBlock) {
+        const int32_t now = b;
+        if (o + kBlock < o1) b = owner(o + kBlock);
+        float x[kD];
+#pragma unroll
+        for (int u = 0; u < kD; ++u) x[u] = g.dX[(int64_t)__shfl(now, u, kD) * kD2 + c];
+#pragma unroll
+        for (int u = 0; u < kD; ++u)
+            if (o + u < o1) v[u] += x[u];
+    }
+#pragma unroll
+    for (int u = 0; u < kD; ++u) acc += v[u];
     row_sums(acc, red, g.gZ + (int64_t)l * kD);
 }
 
@@ -594,11 +596,17 @@ __global__ __launch_bounds__(kBlock) void mlp_grads_kernel(FusedGrads g) {
         return;
     }
     job -= 1;
-    if (job < g.M) {
-        column_grads(g, (int32_t)job, red);
+    if (job < 3 * (int64_t)g.M) {
+        const int32_t col = (int32_t)(job % g.M), t = (int32_t)(job / g.M);
+        if (t == 0)
+            column_grads<kTabF>(g, col, red);
+        else if (t == 1)
+            column_grads<kTabT>(g, col, red);
+        else
+            column_grads<kTabE>(g, col, red);
         return;
     }
-    job -= g.M;
+    job -= 3 * (int64_t)g.M;
     if (job <= g.M) length_grads(g, (int32_t)job, red);
 }
 
@@ -661,7 +669,7 @@ hipError_t fused_rows(const FusedRows &a, hipStream_t s) {
 
 hipError_t fused_grads(const FusedGrads &g, hipStream_t s) {
     const int64_t nS = g.Bp / kChunk;
-    const int64_t jobs = 20 * nS + 3 * (kH / 32) + 1 + g.M + (g.M + 1);
+    const int64_t jobs = 20 * nS + 3 * (kH / 32) + 1 + 3 * (int64_t)g.M + (g.M + 1);
     hipLaunchKernelGGL(mlp_grads_kernel, dim3((unsigned)jobs), dim3(kBlock), 0, s, g);
     return hipGetLastError();
 }
