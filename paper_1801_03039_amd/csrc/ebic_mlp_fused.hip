@@ -25,7 +25,7 @@
 // bf16(relu(z2)), bf16(dz2), bf16(dz1), weights read as BF16 copies.  Every
 // sum has a fixed order, so a step is deterministic on one device.
 //
-// What bounds a step (B = 8192, 500 columns: A 32.5 us, B 18.6, C 4.2; 38.2,
+// What bounds a step (B = 8192, 500 columns: A 32.5 us, B 17.8, C 4.2; 38.2,
 // 34.1 and 4.2 before): the products are small, and each launch lasts as long
 // as its workgroups' chains of dependent loads.  A's tile of 32 candidates is
 // one workgroup of 8 waves (with 4 waves 38.2 us; with each layer's weights
