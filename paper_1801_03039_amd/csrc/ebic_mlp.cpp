@@ -83,15 +83,24 @@ hipError_t dalloc(T *&p, int64_t n) {
         p = nullptr;
         if (e != hipSuccess) return e;
     }
-    return hipMalloc((void **)&p, sizeof(T) * (size_t)std::max<int64_t>(n, 1));
+    const hipError_t e = hipMalloc((void **)&p, sizeof(T) * (size_t)std::max<int64_t>(n, 1));
+    if (e != hipSuccess) {
+        p = nullptr;
+        (void)hipGetLastError();   // reported here, not again by the next launch
+    }
+    return e;
 }
 
 // Buffers of a batch of B candidates, and its lists of L entries (0: none).
+// A group of buffers counts as empty while it is replaced: should one of them
+// fail, the next call allocates all of them again.
 ebic_status reserve(ebic_mlp *m, int64_t B, int64_t L) {
     const int64_t H = m->H, D = m->D;
     if (B > m->cap_B) {
         MHIP(hipStreamSynchronize(m->stream));
         const int64_t c = std::max<int64_t>(B, m->cap_B * 2);
+        m->cap_B = 0;
+        m->last_B = 0;   // the last training call's loss goes with sq
         MHIP(dalloc(m->y, c));
         MHIP(dalloc(m->sq, c));
         MHIP(dalloc(m->len_b, c));
@@ -115,12 +124,14 @@ ebic_status reserve(ebic_mlp *m, int64_t B, int64_t L) {
     if (L > m->cap_L) {
         MHIP(hipStreamSynchronize(m->stream));
         const int64_t c = std::max<int64_t>(L, m->cap_L * 2);
+        m->cap_L = 0;
         MHIP(dalloc(m->occ_pos, c));
         MHIP(dalloc(m->occ_b, c));
         m->cap_L = c;
     }
     const int64_t need_ws = (int64_t)kMaxSplits * std::max<int64_t>(H * H, H * 2 * D);
     if (!m->fused && need_ws > m->cap_ws) {
+        m->cap_ws = 0;
         MHIP(dalloc(m->ws, need_ws));
         m->cap_ws = need_ws;
     }
@@ -140,6 +151,7 @@ ebic_status reserve_fused(ebic_mlp *m, int64_t B) {
     if (Bp <= m->cap_Bp) return EBIC_OK;
     MHIP(hipStreamSynchronize(m->stream));
     const int64_t c = std::max<int64_t>(Bp, m->cap_Bp * 2);
+    m->cap_Bp = 0;
     const int64_t H = m->H, D2 = 2 * m->D;
     const int64_t tiles = c / mlp::fused_tile_rows(), nS = c / mlp::fused_chunk();
     MHIP(dalloc(m->XrT, D2 * c));
@@ -289,8 +301,13 @@ hipError_t reserve_io(ebic_mlp *m, int64_t n) {
     }
     hipError_t e = hipHostMalloc((void **)&m->h_io, sizeof(int32_t) * (size_t)c,
                                  hipHostMallocDefault);
-    if (e == hipSuccess) m->cap_io = c;
-    return e;
+    if (e != hipSuccess) {
+        m->h_io = nullptr;
+        (void)hipGetLastError();
+        return e;
+    }
+    m->cap_io = c;
+    return hipSuccess;
 }
 
 // The lists by column and by length on the host, for networks too wide for
@@ -360,8 +377,8 @@ ebic_status upload(ebic_mlp *m, const int32_t *off, const int32_t *cols, int32_t
     MHIP(hipEventRecord(m->copied, m->stream));
     m->copying = true;
     if (!occurrences) return EBIC_OK;
-    if (!m->occ_start) MHIP(hipMalloc((void **)&m->occ_start, sizeof(int32_t) * ((size_t)m->M + 1)));
-    if (!m->len_start) MHIP(hipMalloc((void **)&m->len_start, sizeof(int32_t) * ((size_t)m->M + 2)));
+    if (!m->occ_start) MHIP(dalloc(m->occ_start, (int64_t)m->M + 1));
+    if (!m->len_start) MHIP(dalloc(m->len_start, (int64_t)m->M + 2));
     if (!mlp::lists_on_device(m->M)) return host_lists(m, off, cols, B);
     const int64_t ws = mlp::lists_workspace(B, L, m->M);
     if (ws > m->cap_lists) {
