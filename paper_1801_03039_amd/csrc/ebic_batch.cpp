@@ -57,6 +57,7 @@ struct ebic_batch {
     int32_t resident_wgs = 0;       // workgroups resident at once (occupancy x CUs)
     int32_t workgroups = 0, unroll = 4, words = 1, whole = 0, use_graph = 0;
     uint64_t static_grid = 0;   // grid of the queue-free mode (largest tile count so far)
+    int32_t static_stage = 0;   // its staging area (largest so far)
     double tuned_ms = 0.0;
     bool tuned = false;
     hipGraphExec_t exec = nullptr;
@@ -133,6 +134,7 @@ struct Request {
     const ebic_params *params = nullptr;
     bool masks = false;
     bool mark_repeats = false;   // series that repeat a column get count -1
+    int32_t longest = 0;         // no series is longer
 };
 
 // Capacity for n candidates / n column entries / mask words.
@@ -168,27 +170,74 @@ bool via_index(const ebic_batch *b, const Request &q, int32_t r) {
     return !b->direct[(size_t)r] && q.params->max_violations <= kIndexMaxViolations;
 }
 
+// How a run's population is cut into tiles: whole candidates (cpw > 0), or 256
+// consecutive (candidate, word-group) items; and the column entries of the
+// tile that needs most of the staging area.
+struct Cut {
+    int32_t cpw = 0;
+    int64_t need = 0;
+};
+
+// Cut of a run of P candidates of `items` groups of `words` words each; off:
+// their P + 1 offsets, no series longer than `longest`.  Tiles of whole
+// candidates hold as many as 256 lanes do.  With 8 words per lane they hold no
+// more than the staging area takes, as the loop that reads its columns from
+// memory then has one pair in flight: 64 runs of 300-500 rows, 1024 series of
+// 10-40 columns, k = 1, both directions, take 18.9 us with half the lanes idle
+// and 20.0 with all of them and columns from memory; with fewer words the idle
+// lanes cost more (1 word, 40-64 rows: 16.0 and 13.5 us).
+Cut cut_run(const int32_t *off, int32_t P, int64_t items, int32_t words, int32_t whole,
+            int32_t longest) {
+    Cut c;
+    c.cpw = whole && items <= 256 ? (int32_t)(256 / items) : 0;
+    c.need = (c.cpw ? c.cpw : 2 + 255 / items) * (int64_t)longest;
+    if (c.need <= kStageMin || items > 128) return c;
+    auto span = [&](int64_t lo, int64_t hi) {   // entries of candidates lo .. hi - 1
+        return (int64_t)off[std::min<int64_t>(hi, P)] - off[lo];
+    };
+    if (!c.cpw) {
+        c.need = 0;
+        for (int64_t i = 0; i < P * items; i += 256)
+            c.need = std::max(c.need, span(i / items, std::min<int64_t>((i + 255) / items + 1, P)));
+        return c;
+    }
+    for (;; c.cpw /= 2) {
+        c.need = 0;
+        for (int64_t i = 0; i < P; i += c.cpw) c.need = std::max(c.need, span(i, i + c.cpw));
+        if (words < 8 || c.need <= kStageMax || c.cpw == 1) return c;
+    }
+}
+
+// Tiles of a run of P candidates of `items` word groups.
+uint64_t tiles_of(int32_t P, int32_t cpw, int64_t items) {
+    return cpw ? ((uint64_t)P + cpw - 1) / cpw : ((uint64_t)P * (uint64_t)items + 255) / 256;
+}
+
 // Fills the run table for a request (tiles of 256 lanes with `words` 64-row
 // words each); returns the total number of tiles.  With `whole`, a run
 // whose candidates take at most 256 lanes each gets tiles of whole
 // candidates (as many as fit); other runs, or all without it, get tiles of
 // 256 consecutive (candidate, word-group) items.  Table entries are in tile
-// order, which is not run order.
-uint64_t fill_runs(ebic_batch *b, const Request &q, int32_t words, int32_t whole) {
+// order, which is not run order.  *stage: the staging area of a workgroup.
+uint64_t fill_runs(ebic_batch *b, const Request &q, int32_t words, int32_t whole,
+                   int32_t *stage) {
     const int32_t R = (int32_t)b->ctx.size();
     std::vector<int64_t> cand((size_t)R), maskw((size_t)R);
     std::vector<int32_t> cpw((size_t)R), order((size_t)R);
-    int64_t c0 = 0, m0 = 0;
+    int64_t c0 = 0, m0 = 0, need = 0;
     for (int32_t r = 0; r < R; ++r) {
         const ebic_ctx *c = b->ctx[(size_t)r];
         cand[(size_t)r] = c0;
         maskw[(size_t)r] = m0;
+        const Cut cut = cut_run(b->h_off + c0, via_index(b, q, r) ? q.P[(size_t)r] : 0,
+                                (c->W + words - 1) / words, words, whole, q.longest);
+        cpw[(size_t)r] = cut.cpw;
+        need = std::max(need, cut.need);
         c0 += q.P[(size_t)r];
         if (q.masks) m0 += (int64_t)q.P[(size_t)r] * 2 * c->W;
-        const uint64_t items = (uint64_t)((c->W + words - 1) / words);
-        cpw[(size_t)r] = (whole && items <= 256) ? (int32_t)(256 / items) : 0;
         order[(size_t)r] = r;
     }
+    *stage = stage_entries(need);
     // Runs with more candidates per tile first: such a tile lasts as long as
     // the longest series among its candidates, so these tiles are the long
     // ones, and the launch ends on the short tiles of tall runs (measured
@@ -204,12 +253,11 @@ uint64_t fill_runs(ebic_batch *b, const Request &q, int32_t words, int32_t whole
         ebic_ctx *c = b->ctx[(size_t)r];
         // a directly evaluated run keeps its place in the launch but gets no tiles
         const int32_t P = via_index(b, q, r) ? q.P[(size_t)r] : 0;
-        const uint64_t items = (uint64_t)((c->W + words - 1) / words);
         const int32_t k = cpw[(size_t)r];
         b->h_runs[i] = IndexRun{c->d_idx, c->d_tie, c->d_log, c->n, c->W, c->wpad, c->m, P, cand[(size_t)r],
                                 maskw[(size_t)r], k, q.params->max_violations, tie_bitmap(c)};
         b->h_tile_base[i] = (uint32_t)tiles;
-        tiles += k ? ((uint64_t)P + k - 1) / k : ((uint64_t)P * items + 255) / 256;
+        tiles += tiles_of(P, k, (c->W + words - 1) / words);
     }
     b->h_tile_base[R] = (uint32_t)tiles;
     return tiles;
@@ -217,11 +265,11 @@ uint64_t fill_runs(ebic_batch *b, const Request &q, int32_t words, int32_t whole
 
 // workgroups < 0: one workgroup per tile, no queue.  A direct launch has
 // exactly one workgroup per tile; a graph launch uses the largest tile count
-// seen since the shape was set (the kernel reads the current count, and
+// (and staging area) seen since the shape was set (the kernel reads the current count, and
 // surplus workgroups return at once), so that the captured graph stays valid
 // from one generation to the next.
 BatchLaunch make_launch(ebic_batch *b, const Request &q, int32_t workgroups, int32_t unroll,
-                        int32_t words, uint64_t tiles) {
+                        int32_t words, uint64_t tiles, int32_t stage) {
     BatchLaunch L{};
     L.runs = b->d_runs;
     L.tile_base = b->d_tile_base;
@@ -248,6 +296,8 @@ BatchLaunch make_launch(ebic_batch *b, const Request &q, int32_t workgroups, int
     } else {
         L.grid = (uint32_t)workgroups;
     }
+    if (b->use_graph) stage = b->static_stage = std::max(b->static_stage, stage);
+    L.stage = stage;
     L.unroll = unroll;
     L.words = words;
     return L;
@@ -259,7 +309,7 @@ bool same_graph(const BatchLaunch &a, const BatchLaunch &x) {
            a.offsets == x.offsets && a.cols == x.cols && a.n_entries == x.n_entries &&
            a.sigma == x.sigma && a.k == x.k && a.negative == x.negative && a.masks == x.masks &&
            a.acc == x.acc && a.counts == x.counts && a.fitness == x.fitness && a.grid == x.grid &&
-           a.unroll == x.unroll && a.words == x.words;
+           a.unroll == x.unroll && a.words == x.words && a.stage == x.stage;
 }
 
 // Graph = [kernel]; the run table is copied before it on the same stream.
@@ -318,7 +368,8 @@ ebic_status time_replays(ebic_batch *b, int32_t reps, double *ms_per_launch) {
 ebic_status run_request(ebic_batch *b, const Request &q, int32_t workgroups, int32_t unroll,
                         int32_t words, int32_t whole, bool copy_back = true) {
     b->has_last = false;
-    const uint64_t tiles = fill_runs(b, q, words, whole);
+    int32_t stage = 0;
+    const uint64_t tiles = fill_runs(b, q, words, whole, &stage);
     const int32_t R = (int32_t)b->ctx.size();
     bool any_direct = false;
     for (int32_t r = 0; r < R; ++r) any_direct |= q.P[(size_t)r] > 0 && !via_index(b, q, r);
@@ -334,7 +385,8 @@ ebic_status run_request(ebic_batch *b, const Request &q, int32_t workgroups, int
     BHIP(hipEventRecord(b->ev0, b->stream));
     if (tiles > 0) {
         const BatchLaunch L =
-            make_launch(b, q, workgroups < 0 ? -1 : std::max(1, workgroups), unroll, words, tiles);
+            make_launch(b, q, workgroups < 0 ? -1 : std::max(1, workgroups), unroll, words, tiles,
+                        stage);
         ebic_status st = launch(b, L);
         if (st != EBIC_OK) return st;
         b->last_launch = L;
@@ -386,8 +438,8 @@ ebic_status run_request(ebic_batch *b, const Request &q, int32_t workgroups, int
 constexpr int32_t kTuneReplays = 5;
 
 ebic_status tune(ebic_batch *b, const Request &q) {
-    const uint64_t tiles = fill_runs(b, q, 1, 0);
-    if (tiles == 0) return EBIC_OK;
+    int32_t stage = 0;
+    if (fill_runs(b, q, 1, 0, &stage) == 0) return EBIC_OK;
     const int32_t full = b->resident_wgs;
     // persistent grids, and one workgroup per tile without a queue (-1)
     std::vector<int32_t> grids = {std::max(1, full / 2), full, 2 * full, -1};
@@ -417,6 +469,7 @@ ebic_status tune(ebic_batch *b, const Request &q) {
     b->words = best_v;
     b->whole = best_w;
     b->static_grid = 0;
+    b->static_stage = 0;
     b->tuned_ms = best;
     b->tuned = true;
     return EBIC_OK;
@@ -476,7 +529,10 @@ ebic_status finish_runs(ebic_batch *b, const ebic_evolve_params *params,
     int64_t n_cols = 0, n_mask = 0;
     std::vector<Pop> tops((size_t)R);
     for (int32_t r = 0; r < R; ++r) {
-        for (const TopEntry &e : top[(size_t)r]) tops[(size_t)r].push(e.s.data(), (int32_t)e.s.size());
+        for (const TopEntry &e : top[(size_t)r]) {
+            tops[(size_t)r].push(e.s.data(), (int32_t)e.s.size());
+            q.longest = std::max(q.longest, (int32_t)e.s.size());
+        }
         q.P[(size_t)r] = tops[(size_t)r].size();
         q.n_cand += q.P[(size_t)r];
         n_cols += tops[(size_t)r].off.back();
@@ -652,6 +708,7 @@ ebic_status ebic_batch_set_tuning(ebic_batch *b, const ebic_batch_tuning *t) {
     b->whole = t->whole_candidates;
     b->use_graph = t->use_graph;
     b->static_grid = 0;
+    b->static_stage = 0;
     b->tuned = true;
     b->tuned_ms = 0.0;
     return EBIC_OK;
@@ -700,6 +757,7 @@ ebic_status ebic_batch_evaluate(ebic_batch *b, const int32_t *const *offsets,
     if (n_cols > INT32_MAX || q.n_cand > INT32_MAX)
         return bfail(EBIC_E_ARG, "batched populations hold more than 2^31 - 1 columns; split them");
     q.n_cols = n_cols;
+    q.longest = longest;
     if (q.n_cand == 0) return EBIC_OK;
     BHIP(hipSetDevice(b->device));
     ebic_status st = reserve(b, q.n_cand, n_cols, n_mask);
@@ -819,6 +877,7 @@ ebic_status ebic_batch_evolve(ebic_batch *b, const uint64_t *seeds, int32_t gene
         });
         Request q;
         q.params = &runs[0]->eval_params();
+        q.longest = params->len_max;
         q.P.assign((size_t)R, 0);
         int64_t n_cols = 0;
         for (int32_t r = 0; r < R; ++r)
@@ -986,14 +1045,19 @@ ebic_status ebic_batch_evolve_device(ebic_batch *b, const uint64_t *seeds, int32
     std::vector<IndexRun> iruns((size_t)R);
     std::vector<uint32_t> tile_base((size_t)R + 1);
     uint64_t tiles = 0;
+    int64_t need = 0;
     for (int32_t r = 0; r < R; ++r) {
         ebic_ctx *c = b->ctx[(size_t)r];
-        const uint64_t items = (uint64_t)((c->W + words - 1) / words);
-        const int32_t cpw = (whole && items <= 256) ? (int32_t)(256 / items) : 0;
+        const int64_t items = (c->W + words - 1) / words;
+        // (lengths are not known here; cut_run's rule at their mean)
+        int32_t cpw = (whole && items <= 256) ? (int32_t)(256 / items) : 0;
+        while (words == 8 && cpw > 1 && (int64_t)cpw * (params->len_min + slot) / 2 > kStageMax)
+            cpw /= 2;
+        need = std::max(need, (cpw ? cpw : 2 + 255 / items) * (int64_t)slot);
         iruns[(size_t)r] = IndexRun{c->d_idx, c->d_tie, c->d_log, c->n, c->W, c->wpad, c->m, P, r * stride,
                                     0, cpw, params->eval.max_violations, tie_bitmap(c)};
         tile_base[(size_t)r] = (uint32_t)tiles;
-        tiles += cpw ? ((uint64_t)P + cpw - 1) / cpw : ((uint64_t)P * items + 255) / 256;
+        tiles += tiles_of(P, cpw, items);
     }
     tile_base[(size_t)R] = (uint32_t)tiles;
     if (tiles > 0x7FFFFFFFull) return bfail(EBIC_E_ARG, "batched populations too large for one launch");
@@ -1019,6 +1083,7 @@ ebic_status ebic_batch_evolve_device(ebic_batch *b, const uint64_t *seeds, int32
     L.grid = (uint32_t)tiles;
     L.unroll = unroll;
     L.words = words;
+    L.stage = stage_entries(need);
 
     StepsArgs A{};
     A.runs = d_sruns;

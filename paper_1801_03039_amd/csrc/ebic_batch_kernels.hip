@@ -21,24 +21,32 @@ namespace {
 constexpr int kRunsLds = 1024;   // tile bases kept in LDS (more runs: read from memory)
 static_assert(sizeof(IndexRun) % 8 == 0, "run descriptor copied as 8-byte words");
 
+// Waves per SIMD that the registers leave room for in instances that would
+// otherwise take a few registers more than that (79-81, 95-99 VGPRs).
+constexpr int min_waves(int K, bool NEG, int V) {
+    return K == 0 && NEG && V == 1 ? 6 : (K == 0 && NEG && V == 2) || (K == 1 && !NEG && V == 4) ? 5 : 1;
+}
+
 template <int K, bool NEG, int U, int V>
-__global__ __launch_bounds__(kBlock) void eval_index_batch_kernel(
+__global__ __launch_bounds__(kBlock, min_waves(K, NEG, V)) void eval_index_batch_kernel(
     const IndexRun *__restrict__ runs, const uint32_t *__restrict__ tile_base, int32_t n_runs,
     unsigned int *__restrict__ work, const int32_t *__restrict__ offsets,
     const int32_t *__restrict__ cols, int64_t n_entries, int32_t sigma,
     uint64_t *__restrict__ masks, unsigned long long *__restrict__ acc,
-    int32_t *__restrict__ counts, double *__restrict__ fitness) {
+    int32_t *__restrict__ counts, double *__restrict__ fitness, int32_t stage_n) {
     __shared__ uint32_t s_tb[kRunsLds + 1];
     __shared__ IndexRun s_R;
     __shared__ TileLds lds;
+    extern __shared__ uint64_t s_stage[];
+    const StageLds stage(s_stage, stage_n);
     // A run's tiles hold whole candidates (cpw > 0) or flattened items.
     auto tile = [&](const IndexRun &R, uint32_t local) {
         if (R.cpw > 0)
             index_tile<K, NEG, U, V, true>(R, local, (uint32_t)R.cpw, offsets, cols, n_entries,
-                                           sigma, masks, acc, counts, fitness, lds);
+                                           sigma, masks, acc, counts, fitness, lds, stage);
         else
             index_tile<K, NEG, U, V, false>(R, local, 0, offsets, cols, n_entries, sigma, masks,
-                                            acc, counts, fitness, lds);
+                                            acc, counts, fitness, lds, stage);
     };
     __shared__ uint32_t s_tile, s_local;
     __shared__ int32_t s_run;
@@ -100,7 +108,7 @@ __global__ __launch_bounds__(kBlock) void eval_index_batch_kernel(
         if (tid == 0) next = atomicAdd(work, 1u);
         __syncthreads();
         tile(s_R, s_local);
-        __syncthreads();  // every wave is done with s_R, s_local and s_cols
+        __syncthreads();  // every wave is done with s_R, s_local and the staged columns
     }
     if (tid == 0) {
         const unsigned left = atomicAdd(work + 1, 1u);
@@ -115,14 +123,15 @@ __global__ __launch_bounds__(kBlock) void eval_index_batch_kernel(
 
 template <int K, int U, int V>
 static void launch_batch_k(const BatchLaunch &b, hipStream_t stream) {
+    const unsigned lds = stage_bytes(b.stage);
     if (b.negative)
-        hipLaunchKernelGGL((eval_index_batch_kernel<K, true, U, V>), dim3(b.grid), dim3(kBlock), 0,
+        hipLaunchKernelGGL((eval_index_batch_kernel<K, true, U, V>), dim3(b.grid), dim3(kBlock), lds,
                            stream, b.runs, b.tile_base, b.n_runs, b.work, b.offsets, b.cols,
-                           b.n_entries, b.sigma, b.masks, b.acc, b.counts, b.fitness);
+                           b.n_entries, b.sigma, b.masks, b.acc, b.counts, b.fitness, b.stage);
     else
         hipLaunchKernelGGL((eval_index_batch_kernel<K, false, U, V>), dim3(b.grid), dim3(kBlock),
-                           0, stream, b.runs, b.tile_base, b.n_runs, b.work, b.offsets, b.cols,
-                           b.n_entries, b.sigma, b.masks, b.acc, b.counts, b.fitness);
+                           lds, stream, b.runs, b.tile_base, b.n_runs, b.work, b.offsets, b.cols,
+                           b.n_entries, b.sigma, b.masks, b.acc, b.counts, b.fitness, b.stage);
 }
 
 template <int U, int V>
@@ -163,7 +172,8 @@ int batch_wgs_per_cu() {
     int blocks = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks,
                                                      eval_index_batch_kernel<1, true, 4, 1>,
-                                                     kBlock, 0) != hipSuccess || blocks < 1)
+                                                     kBlock, stage_bytes(kStageMin)) != hipSuccess ||
+        blocks < 1)
         blocks = 1;
     return blocks;
 }

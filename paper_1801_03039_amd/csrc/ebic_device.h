@@ -104,15 +104,15 @@ __device__ __forceinline__ void finish_part(int64_t c, uint32_t cnt, bool bad, i
 // may tie (a set bit of the tie-pair bitmap).
 //
 // Two loops.  The fast one serves workgroups whose columns all lie in the
-// matrix and whose pairs never tie, which staging finds out: there a pair
-// costs one LDS read (the byte or 128-byte offsets of its order row, formed
-// once per staged column), one address and 2 to 3 operations per half-word
-// and direction, and no column is checked.  The general one serves the rest
-// (tied pairs, malformed candidates, series past the staging area).  Loads
+// matrix and of whose pairs few tie, which staging finds out: there a pair
+// costs one LDS read (the two offsets of its columns, formed once per staged
+// column), one address and 2 to 3 operations per half-word and direction, and
+// no column is checked; the few tied pairs are counted before it.  The general
+// one serves the rest (many tied pairs, malformed candidates, series past the
+// staging area, whose columns it reads from memory).  Loads
 // for U pairs are issued before any is consumed (the lane's latency chain is
 // one order-word round trip per U pairs), and a lane stops once every row of
 // its words is rejected in every enabled direction.
-constexpr int kPreLds = 2048;   // staged column entries per workgroup
 constexpr int kUnroll = 4;   // pairs per batch of loads (single-run default)
 constexpr int kWordsPerLane = 2;   // 64-row words per lane (flattened single-run tiling)
 
@@ -226,19 +226,25 @@ struct PreCol {
     uint32_t row, col;
 };
 
-// LDS of one tile: the staged CBF columns, for whole-candidate tiles the
-// per-candidate row counts and malformed flags, the tie-pair bitmap, and
-// what staging found.
+// LDS of one tile: for whole-candidate tiles the per-candidate row counts and
+// malformed flags, the tie-pair bitmap, and what staging found.
 struct TileLds {
-    PreCol pre[kPreLds];
     int32_t rows[kBlock];
     int32_t bad[kBlock];
     uint32_t tbits[kTieWords];
-    uint64_t tied[kPreLds / 64];   // bit e % 64 of word e / 64: staged column e may
-                                   // tie with the one before it, or repeats it
     uint32_t found;                // what staging found (kFound*)
-    uint32_t n_tied;               // bits set in `tied`
+    uint32_t n_tied;               // bits set in StageLds::tied
 };
+// The launch's staging area of `entries` columns (a multiple of 64) behind it.
+struct StageLds {
+    PreCol *pre;
+    uint64_t *tied;   // bit e % 64 of word e / 64: staged column e may tie with
+                      // the one before it, or repeats it
+    int32_t entries;
+    __device__ StageLds(uint64_t *lds, int32_t n)
+        : pre(reinterpret_cast<PreCol *>(lds)), tied(lds + n), entries(n) {}
+};
+static_assert(sizeof(PreCol) == sizeof(uint64_t), "one word of the staging area per column");
 constexpr uint32_t kFoundBad = 1;    // a staged column is out of range, or a lane's
                                      // series lies outside the staged span
 constexpr uint32_t kFoundTied = 2;   // a staged pair may tie
@@ -298,7 +304,8 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
                                            int32_t sigma, uint64_t *__restrict__ masks,
                                            unsigned long long *__restrict__ acc,
                                            int32_t *__restrict__ counts,
-                                           double *__restrict__ fitness, TileLds &lds) {
+                                           double *__restrict__ fitness, TileLds &lds,
+                                           const StageLds &stage) {
     // (V <= 8 keeps a wave's per-candidate row count within 16 bits below)
     static_assert(V == 1 || V == 2 || V == 4 || V == 8, "words per lane");
     const auto idx = as_global(R.idx);
@@ -357,33 +364,81 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
         s_rows[tid] = 0;
         s_bad[tid] = 0;
     }
-    // row strides of the staged offsets; the unit form has to fit 32 bits
+    // row strides of the offsets of order rows (the unit form fits 32 bits up
+    // to an index of 512 GiB)
     const uint32_t col_s = OFF32 ? (uint32_t)wpad * 8u : (uint32_t)(wpad / 16);
     const uint32_t row_s = (uint32_t)m * col_s;
-    const bool staged = b0 >= 0 && b1 <= n_entries && b1 >= b0 && b1 - b0 <= kPreLds &&
-                        (OFF32 || (uint64_t)m * (uint64_t)m * (uint64_t)(wpad / 16) < (1ull << 32));
+    const bool staged = b0 >= 0 && b1 <= n_entries && b1 >= b0 && b1 - b0 <= stage.entries;
     const int32_t span = staged ? (int32_t)(b1 - b0) : 0;
     __syncthreads();   // lds.found is cleared, the bitmap is in LDS
     bool wrong = staged && ok_range && (start < b0 || end > b1);
     uint32_t n_tied = 0;
-    for (int32_t e = tid; (e & ~63) < span; e += (int32_t)blockDim.x) {   // whole waves
-        const bool in_span = e < span;
-        const int32_t x = in_span ? cols[b0 + e] : 0;
-        int32_t xp = -1;
-        if constexpr (NEG) xp = in_span && e > 0 ? cols[b0 + e - 1] : -1;
-        const bool in = x >= 0 && x < m;
-        wrong |= in_span && !in;
-        if (in_span) lds.pre[e] = PreCol{(uint32_t)x * row_s, (uint32_t)x * col_s};
-        // pairs that straddle two candidates included (no series reads them)
+    // N entries per lane, blockDim.x apart, whose reads are all in flight
+    // together (entries past the span repeat its last one).
+    auto stage_entries = [&](auto per_lane, auto look_up_ties, int32_t e0) {
+        constexpr int N = decltype(per_lane)::value;
+        constexpr bool TIES = decltype(look_up_ties)::value;
+        int32_t x[N];
+        uint32_t tie[N];   // of the pair that ends in the entry
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            x[u] = cols[b0 + min(e0 + u * (int32_t)blockDim.x, span - 1)];
         if constexpr (NEG) {
-            const bool pair = in_span && in && xp >= 0 && xp < m;
-            const int64_t pq = (int64_t)xp * m + x;
-            const uint64_t t = ballot(
-                pair && (x == xp || (ties && in_bitmap(pq) && as_global(R.tie)[pq] != 0)));
-            n_tied += (uint32_t)__popcll(t);
-            if (lane == 0) lds.tied[e >> 6] = t;
+            int64_t pq[N];   // -1: no pair
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const int32_t e = min(e0 + u * (int32_t)blockDim.x, span);
+                const int32_t xp = cols[b0 + max(min(e, span - 1) - 1, 0)];
+                // pairs that straddle two candidates included (no series reads them)
+                const bool pair = e > 0 && e < span && (uint32_t)x[u] < (uint32_t)m &&
+                                  (uint32_t)xp < (uint32_t)m;
+                pq[u] = pair ? (int64_t)xp * m + x[u] : -1;
+                tie[u] = pair && x[u] == xp;
+            }
+            if constexpr (TIES) {
+                bool any = false;
+#pragma unroll
+                for (int u = 0; u < N; ++u) {
+                    pq[u] = pq[u] >= 0 && in_bitmap(pq[u]) ? pq[u] : -1;
+                    any |= pq[u] >= 0;
+                }
+                if (ballot(any) != 0ull) {   // (few waves, if few pairs tie)
+                    uint32_t flag[N];        // (a clear bit reads flag 0, whatever it says)
+#pragma unroll
+                    for (int u = 0; u < N; ++u) flag[u] = as_global(R.tie)[max(pq[u], int64_t{0})];
+#pragma unroll
+                    for (int u = 0; u < N; ++u) tie[u] |= pq[u] >= 0 ? flag[u] : 0u;
+                }
+            }
         }
-    }
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int32_t e = e0 + u * (int32_t)blockDim.x;
+            if ((e & ~63) >= span) break;   // whole waves
+            wrong |= e < span && (uint32_t)x[u] >= (uint32_t)m;
+            if (e < span) stage.pre[e] = PreCol{(uint32_t)x[u] * row_s, (uint32_t)x[u] * col_s};
+            if constexpr (NEG) {
+                const uint64_t t = ballot(tie[u] != 0u);
+                n_tied += (uint32_t)__popcll(t);
+                if (lane == 0) stage.tied[e >> 6] = t;
+            }
+        }
+    };
+    // Several entries per lane at a time (a workgroup of few lanes and many
+    // series has many), fewer where ties are looked up, for the registers.
+    auto stage_span = [&](auto look_up_ties) {
+        constexpr int N = decltype(look_up_ties)::value ? 2 : 4;
+        for (int32_t e = tid; (e & ~63) < span; e += N * (int32_t)blockDim.x) {
+            if ((e & ~63) + (int32_t)blockDim.x < span)
+                stage_entries(std::integral_constant<int, N>{}, look_up_ties, e);
+            else
+                stage_entries(std::integral_constant<int, 1>{}, look_up_ties, e);
+        }
+    };
+    if (NEG && ties)
+        stage_span(std::integral_constant<bool, NEG>{});
+    else
+        stage_span(std::false_type{});
     {
         const uint32_t f = (ballot(wrong) != 0ull ? kFoundBad : 0u) |
                            (n_tied != 0u ? kFoundTied : 0u);
@@ -414,9 +469,20 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
     // The lane of a candidate's first word reports whether it is malformed.
     bool bad = active && g == 0 && !ok_range;
 
+    // The lane's words (from its v-th on) of the order row at a staged offset.
+    typedef const __attribute__((address_space(1))) char *gchar;
+    const auto base = OFF32 ? (gchar)idx : (gchar)(idx + w0);
+    const uint32_t w_off = OFF32 ? (uint32_t)w0 * 8u : 0u;
+    auto row_at = [&](uint32_t off, uint32_t v) {
+        if constexpr (OFF32)
+            return (global_ptr<uint64_t>)(base + (off + (w_off + v * 8u)));
+        else
+            return (global_ptr<uint64_t>)(base + (((uint64_t)off << 7) + v * 8u));
+    };
+
     if (good && !many_ties) {
         if (any_valid) {
-            const PreCol *const pre = lds.pre + lds0;
+            const PreCol *const pre = stage.pre + lds0;
             constexpr bool REST_FIRST = K > 1;
             Violations<K> cu[V][2], cd[V][2];   // rising, falling; low and high half-word
 #pragma unroll
@@ -437,18 +503,10 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
                     live |= valid[v] & ~(NEG ? (over(cu, v) & over(cd, v)) : over(cu, v));
                 return live != 0ull;
             };
-            typedef const __attribute__((address_space(1))) char *gchar;
-            const auto words = OFF32 ? (gchar)idx : (gchar)(idx + w0);
-            const uint32_t w_off = OFF32 ? (uint32_t)w0 * 8u : 0u;
             // The order words of N pairs, pair i(u) in slot u: the offset
             // reads and loads are all issued before any word is consumed.
             uint64_t lt[U][V];
-            auto load_row = [&](uint32_t off, uint64_t (&o)[V]) {
-                if constexpr (OFF32)
-                    load_words<V>((global_ptr<uint64_t>)(words + (off + w_off)), o);
-                else
-                    load_words<V>((global_ptr<uint64_t>)(words + ((uint64_t)off << 7)), o);
-            };
+            auto load_row = [&](uint32_t off, uint64_t (&o)[V]) { load_words<V>(row_at(off, 0), o); };
             auto load = [&](auto n_pairs, auto &&i) {
 #pragma unroll
                 for (int u = 0; u < decltype(n_pairs)::value; ++u)
@@ -491,7 +549,7 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
             if (NEG && (found & kFoundTied) != 0) {
                 const int32_t e0 = lds0 + 1, e1 = lds0 + L;   // pairs end in staged columns [e0, e1)
                 for (int32_t wi = e0 >> 6; wi < (e1 + 63) >> 6; ++wi) {
-                    uint64_t bits = lds.tied[wi];
+                    uint64_t bits = stage.tied[wi];
                     if (wi == e0 >> 6) bits &= ~0ull << (e0 & 63);
                     if (wi == e1 >> 6) bits &= ~(~0ull << (e1 & 63));
                     while (bits != 0ull) {
@@ -503,8 +561,8 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
                             have[u] = bits != 0ull;
                             e[u] = have[u] ? wi * 64 + __builtin_ctzll(bits) : e0;
                             bits &= bits - 1;
-                            load_row(lds.pre[e[u] - 1].row + lds.pre[e[u]].col, o[u][0]);
-                            load_row(lds.pre[e[u]].row + lds.pre[e[u] - 1].col, o[u][1]);
+                            load_row(stage.pre[e[u] - 1].row + stage.pre[e[u]].col, o[u][0]);
+                            load_row(stage.pre[e[u]].row + stage.pre[e[u] - 1].col, o[u][1]);
                         }
 #pragma unroll
                         for (int u = 0; u < 2; ++u)
@@ -546,19 +604,28 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
             }
         }
     } else {
-        // Both order rows of every pair, each direction from its own, at most
-        // four words at a time so that this loop needs no more registers than
-        // the fast one.  pair_at(t, rising): offset (in words) of the order
-        // row of the series' pair that ends at position t, or its reverse's.
-        constexpr int VV = V < 4 ? V : 4, UU = U < 4 / VV ? U : 4 / VV;
-        auto by_words = [&](auto &&pair_at) {
+        // The rising direction from the pair's order row, the falling one from
+        // the reverse's or, where it is known not to tie, from the same row
+        // again (it falls where it does not rise); four words at a time (all 8
+        // where the fast loop has two pairs of 8 in flight), so that this loop
+        // needs no more registers than the fast one.  rows_at(t, pair) calls
+        // pair(u, up, down, tied) for the UU pairs that end at positions t,
+        // t + 1, ... with the offsets (as staged) of their order rows and of
+        // their reverses' (past the series' end any row).
+        constexpr int VV = V == 8 && U > 1 ? 8 : (V < 4 ? V : 4);
+        constexpr int PAIRS = VV >= 4 || K > 3 ? 1 : (U < 4 / VV ? U : 4 / VV);
+        auto by_words = [&](auto pairs, auto &&rows_at) {
+            constexpr int UU = decltype(pairs)::value;
 #pragma clang loop unroll(disable)
             for (int v0 = 0; v0 < V; v0 += VV) {
                 uint64_t rows_v[VV];
 #pragma unroll
                 for (int v = 0; v < VV; ++v)
-                    rows_v[v] = (active && ok_range && w0 + v0 + v < W)
-                                    ? tail_bits(n, w0 + v0 + v, W) : 0ull;
+                    if constexpr (VV == V)
+                        rows_v[v] = valid[v];
+                    else
+                        rows_v[v] = (active && ok_range && w0 + v0 + v < W)
+                                        ? tail_bits(n, w0 + v0 + v, W) : 0ull;
                 if (rows_v[0] == 0ull) break;   // no words past the last one
                 Violations<K> cu[VV][2], cd[VV][2];
 #pragma unroll
@@ -571,16 +638,15 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
                 auto over = [](const Violations<K> (&c)[2]) -> uint64_t {
                     return ((uint64_t)c[1].c[OVER] << 32) | c[0].c[OVER];
                 };
-                const auto words = idx + w0 + v0;
                 bool more = true;
                 for (int32_t t = 1; t < L && more; t += UU) {
                     uint64_t lu[UU][VV], ld[UU][VV];
-#pragma unroll
-                    for (int u = 0; u < UU; ++u) {   // surplus slots repeat the last pair
-                        const int32_t i = min(t + u, L - 1);
-                        load_words<VV>(words + pair_at(i, true), lu[u]);
-                        if (NEG) load_words<VV>(words + pair_at(i, false), ld[u]);
-                    }
+                    uint32_t flip[UU];
+                    rows_at(t, [&](int u, uint32_t up_at, uint32_t down_at, bool tied) {
+                        load_words<VV>(row_at(up_at, (uint32_t)v0), lu[u]);
+                        if (NEG) load_words<VV>(row_at(tied ? down_at : up_at, (uint32_t)v0), ld[u]);
+                        flip[u] = tied ? ~0u : 0u;
+                    });
 #pragma unroll
                     for (int u = 0; u < UU; ++u) {
                         const uint32_t in = t + u < L ? ~0u : 0u;
@@ -589,7 +655,7 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
 #pragma unroll
                             for (int h = 0; h < 2; ++h) {
                                 cu[v][h].add(~half(lu[u][v], h) & in);
-                                if (NEG) cd[v][h].add(~half(ld[u][v], h) & in);
+                                if (NEG) cd[v][h].add((half(ld[u][v], h) ^ flip[u]) & in);
                             }
                     }
                     uint64_t live = 0;
@@ -607,26 +673,52 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
             }
         };
         if (good) {
-            constexpr int64_t unit = OFF32 ? 1 : 128;   // offsets in bytes or 128 bytes
-            by_words([&](int32_t t, bool rising) -> int64_t {
-                const PreCol p = lds.pre[lds0 + t - 1], q = lds.pre[lds0 + t];
-                return (int64_t)(rising ? p.row + q.col : q.row + p.col) * unit / 8;
-            });
+            by_words(
+                std::integral_constant<int, PAIRS>{}, [&](int32_t t, auto &&pair) {
+#pragma unroll
+                    for (int u = 0; u < PAIRS; ++u) {
+                        const int32_t i = lds0 + min(t + u, L - 1);
+                        const PreCol p = stage.pre[i - 1], q = stage.pre[i];
+                        pair(u, p.row + q.col, q.row + p.col, NEG);
+                    }
+                });
         } else {
             // columns from global memory, clamped so that no read leaves the
             // index; the lane of the candidate's first word checks them all
-            if (active && g == 0)
-                for (int32_t t = 0; t < L; ++t) {
-                    const int32_t x = cols[start + t];
-                    bad |= x < 0 || x >= m;
+            if (active && g == 0) {
+                constexpr int kAhead = V < 4 ? 8 : 2;   // (registers)
+                for (int32_t t = 0; t < L; t += kAhead) {
+                    int32_t x[kAhead];
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) x[u] = cols[start + min(t + u, L - 1)];
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) bad |= x[u] < 0 || x[u] >= m;
                 }
-            auto col = [&](int32_t t) -> int64_t {
-                const int32_t x = cols[start + t];
-                return x < 0 || x >= m ? 0 : x;
+            }
+            auto col = [&](int32_t t) -> uint32_t {
+                const int32_t x = cols[start + min(t, L - 1)];
+                return x < 0 || x >= m ? 0u : (uint32_t)x;
             };
-            by_words([&](int32_t t, bool rising) -> int64_t {
-                return (rising ? col(t - 1) * m + col(t) : col(t) * m + col(t - 1)) * wpad;
-            });
+            // (the columns of the next pairs are read while the rows of these
+            // are under way)
+            constexpr int UU = PAIRS > 1 ? PAIRS / 2 : 1;
+            uint32_t p = 0, next[UU];
+            by_words(
+                std::integral_constant<int, UU>{}, [&](int32_t t, auto &&pair) {
+                    if (t == 1) {
+                        p = col(0);
+#pragma unroll
+                        for (int u = 0; u < UU; ++u) next[u] = col(1 + u);
+                    }
+#pragma unroll
+                    for (int u = 0; u < UU; ++u) {
+                        pair(u, p * row_s + next[u] * col_s, next[u] * row_s + p * col_s,
+                             ties || p == next[u]);
+                        p = next[u];
+                    }
+#pragma unroll
+                    for (int u = 0; u < UU; ++u) next[u] = col(t + UU + u);
+                });
         }
     }
 

@@ -93,6 +93,21 @@ struct IndexRun {
     const uint32_t *tbits;   // tie-pair bitmap (nullptr: no two distinct columns tie)
 };
 
+// Staging area of an evaluator's workgroup (column entries, in LDS; 8 bytes
+// and a bit each): kStageMin serves most shapes and leaves the kernels their
+// resident waves (16.3 of 160 KiB); workgroups of many or long series get up
+// to kStageMax, and past that read the columns from memory.  4096 series of
+// 50-62 columns on 320 rows, rising, k = 0, take 5.0 us with an area of
+// kStageMax; with kStageMin, and columns read from memory one pair at a time,
+// 9.4.
+constexpr int32_t kStageMin = 2048, kStageMax = 4096;
+// The area for workgroups that need `need` entries, and its bytes.
+inline int32_t stage_entries(int64_t need) {
+    if (need <= kStageMin) return kStageMin;
+    return need >= kStageMax ? kStageMax : (int32_t)((need + 255) / 256 * 256);
+}
+inline unsigned stage_bytes(int32_t entries) { return 8u * (unsigned)(entries + entries / 64); }
+
 // Batched launch shapes: unroll x words per lane is at most this.
 constexpr int kMaxUnrollWords = 16;
 
@@ -115,6 +130,7 @@ struct BatchLaunch {
     uint32_t grid;     // persistent workgroups, or the tile count when work is null
     int32_t unroll;    // pairs per batch of loads: 2, 4 or 8
     int32_t words;     // 64-row words per lane: 1 or 2 (a tile is 256 lanes)
+    int32_t stage;     // column entries of a workgroup's staging area
 };
 // work == nullptr selects one tile per workgroup (no queue, grid = tiles).
 

@@ -119,7 +119,9 @@ ebic_status build_index(ebic_ctx *ctx) {
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     if (!ctx->d_idx) {
         void *p = nullptr;
-        hipError_t e = hipMalloc(&p, (size_t)ctx->m * (size_t)ctx->m * (size_t)ctx->wpad * 8);
+        // (the evaluators' row offsets count 128-byte units in 32 bits: 512 GiB)
+        const size_t words = (size_t)ctx->m * (size_t)ctx->m * (size_t)ctx->wpad;
+        hipError_t e = words / 16 <= UINT32_MAX ? hipMalloc(&p, words * 8) : hipErrorOutOfMemory;
         if (e != hipSuccess) {
             (void)hipGetLastError();
             return fail(ctx, EBIC_E_NOMEM, "cannot allocate the pairwise order index (" +
