@@ -450,8 +450,16 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
     __syncthreads();
     const uint32_t found = __builtin_amdgcn_readfirstlane(lds.found);
     const bool good = staged && (found & kFoundBad) == 0;
+    // Tied pairs cost the fast loop both their order rows again, the general
+    // one the reverse's; that one has fewer pairs in flight.  2048 series,
+    // k = 0, both directions, a share of the pairs tied: 20000 rows, 2 words
+    // per lane, 2%: fast 7.7, general 7.9 us; 10%: 9.0 and 8.1; 20%: 10.7 and
+    // 8.5; 30000 rows, 4 words, 2%: 11.0 and 11.3; 5%: 11.8 and 11.3; 10%:
+    // 12.8 and 11.4 (but a launch of both kinds of workgroup lasts as long as
+    // the slower one: matrices with a tie here and there stay with the fast).
+    constexpr uint32_t kTiedShare = V < 4 ? 8 : 12;
     const bool many_ties = NEG && (found & kFoundTied) != 0 &&
-                           __builtin_amdgcn_readfirstlane(lds.n_tied) * 4u > (uint32_t)span;
+                           __builtin_amdgcn_readfirstlane(lds.n_tied) * kTiedShare > (uint32_t)span;
     const int32_t lds0 = (int32_t)(start - b0);
 
     uint64_t valid[V];
@@ -605,8 +613,9 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
         }
     } else {
         // The rising direction from the pair's order row, the falling one from
-        // the reverse's or, where it is known not to tie, from the same row
-        // again (it falls where it does not rise); four words at a time (all 8
+        // the reverse's where the pair may tie (with 1 word per lane always)
+        // and otherwise from the same row again (it falls where it does not
+        // rise); four words at a time (all 8
         // where the fast loop has two pairs of 8 in flight), so that this loop
         // needs no more registers than the fast one.  rows_at(t, pair) calls
         // pair(u, up, down, tied) for the UU pairs that end at positions t,
@@ -679,7 +688,8 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
                     for (int u = 0; u < PAIRS; ++u) {
                         const int32_t i = lds0 + min(t + u, L - 1);
                         const PreCol p = stage.pre[i - 1], q = stage.pre[i];
-                        pair(u, p.row + q.col, q.row + p.col, NEG);
+                        pair(u, p.row + q.col, q.row + p.col,
+                             NEG && (V == 1 || ((stage.tied[i >> 6] >> (i & 63)) & 1ull) != 0ull));
                     }
                 });
         } else {
