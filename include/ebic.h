@@ -462,7 +462,8 @@ ebic_status ebic_batch_evaluate(ebic_batch *b, const int32_t *const *offsets,
  * picks the hardware concurrency.  The launch shape is tuned on the first
  * generation unless set before. */
 /* Device time (ms) of the last batched launch: the kernel, from events on
- * the batch's stream around its launch (the run table is copied before). */
+ * the batch's stream around its launch (the run table is copied before;
+ * a refused population leaves the value of the launch before). */
 double ebic_batch_last_ms(const ebic_batch *b);
 /* Device time (ms) spent building the runs' pairwise order indexes at
  * ebic_batch_create (sum over runs, from events around each build). */
@@ -472,8 +473,9 @@ double ebic_batch_index_build_ms(const ebic_batch *b);
  * device time per launch in ms, from events around the replays: the
  * kernel's own duration without per-call copies and synchronisation, for
  * profiling and launch-shape comparisons (the autotuner uses it).  Errors:
- * E_ARG (null, reps < 1, or no launch since the batch was created or since
- * a request with no candidates), E_DEVICE. */
+ * E_ARG (null, reps < 1, or no launch since the batch was created, since a
+ * request with no candidates, or since a refused population that took the
+ * place of the last launch's), E_DEVICE. */
 ebic_status ebic_batch_time_replays(ebic_batch *b, int32_t reps, double *ms_per_launch);
 
 typedef void (*ebic_batch_generation_fn)(void *user, int32_t run, int32_t gen,

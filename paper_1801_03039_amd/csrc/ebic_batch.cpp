@@ -103,7 +103,8 @@ ebic_status dgrow(ebic_batch *b, T *&p, int64_t need, int64_t &cap, bool zero) {
     if (need <= cap) return EBIC_OK;
     const int64_t ncap = std::max<int64_t>(need, cap * 2);
     BHIP(hipStreamSynchronize(b->stream));
-    drop_graph(b);  // the graph holds the old pointers
+    drop_graph(b);  // the graph and the last launch hold the old pointers
+    b->has_last = false;
     if (p) BHIP(hipFree(p));
     p = nullptr;
     cap = 0;
@@ -802,14 +803,22 @@ ebic_status ebic_batch_evaluate(ebic_batch *b, const int32_t *const *offsets,
     b->h_off[q.n_cand] = (int32_t)n_cols;
     if (tune_now && (st = tune(b, q)) != EBIC_OK) return st;
     q.mark_repeats = check_after;
-    if ((st = run_request(b, q, b->workgroups, b->unroll, b->words, b->whole)) != EBIC_OK) return st;
-    if (check_after && any_negative(b->h_counts, q.n_cand)) {
+    const double last_ms = b->last_ms;
+    st = run_request(b, q, b->workgroups, b->unroll, b->words, b->whole);
+    if (check_after && (st != EBIC_OK || any_negative(b->h_counts, q.n_cand))) {
+        // (a refusal comes before any other error of the launch)
         for (int32_t r = 0; r < R; ++r)
-            if (q.P[(size_t)r] && any_negative(b->h_counts + cand_base[(size_t)r], q.P[(size_t)r]))
+            if (q.P[(size_t)r])
                 (void)valid_cbf(b->ctx[(size_t)r], offsets[r], cols[r], q.P[(size_t)r],
                                 &run_st[(size_t)r]);
-        if ((st = refused()) != EBIC_OK) return st;
+        const ebic_status refusal = refused();
+        if (refusal != EBIC_OK) {
+            b->has_last = false;   // a refused population is not replayed
+            b->last_ms = last_ms;
+            return refusal;
+        }
     }
+    if (st != EBIC_OK) return st;
     int64_t cand = 0, mw = 0;
     for (int32_t r = 0; r < R; ++r) {
         const int32_t n = q.P[(size_t)r];

@@ -188,6 +188,18 @@ ebic_status build_index(ebic_ctx *ctx) {
     return EBIC_OK;
 }
 
+// Back to a context without an index.
+void drop_index(ebic_ctx *ctx) {
+    (void)hipStreamSynchronize(ctx->stream);
+    if (ctx->d_idx) (void)hipFree(ctx->d_idx);
+    if (ctx->d_tie) (void)hipFree(ctx->d_tie);
+    ctx->d_idx = nullptr;
+    ctx->d_tie = nullptr;
+    ctx->any_tie = false;
+    ctx->idx_ms = 0.0;
+    ctx->idx_built = false;
+}
+
 bool params_ok(ebic_ctx *ctx, const ebic_params *p, ebic_status *st) {
     if (!p || p->struct_size < sizeof(ebic_params)) {
         *st = fail(ctx, EBIC_E_ARG, "params is null or struct_size too small");
@@ -454,6 +466,59 @@ bool pack_valid_cbf(ebic_ctx *ctx, const int32_t *offsets, const int32_t *cols, 
 }
 }  // namespace ebic
 
+namespace ebic {
+namespace {
+// Evaluates a host population whose offsets are in order: results in
+// ctx->h_res (fitness, then counts), masks in the caller's array.  With
+// mark_repeats, series that repeat a column get the count -1 too.
+ebic_status evaluate_host(ebic_ctx *ctx, const int32_t *offsets, const int32_t *cols, int32_t P,
+                          const ebic_params *params, uint64_t *masks, bool mark_repeats) {
+    ebic_status st;
+    const int64_t n_entries = offsets[P];
+    // One upload (offsets then columns) and one download (fitness then
+    // counts), both through pinned staging buffers.
+    const int64_t n_cbf = (int64_t)P + 1 + n_entries;      // int32
+    const int64_t n_res = (int64_t)P + ((int64_t)P + 1) / 2;  // doubles: P fitness + P int32
+    HIP_TRY(ctx, hipSetDevice(ctx->device));
+    if ((st = ensure_scratch(ctx, P)) != EBIC_OK) return st;
+    if ((st = grow(ctx, ctx->d_cbf, ctx->cap_cbf, n_cbf, false)) != EBIC_OK) return st;
+    if ((st = grow(ctx, ctx->d_res, ctx->cap_res, n_res, false)) != EBIC_OK) return st;
+    if ((st = grow_pinned(ctx, ctx->h_cbf, ctx->hcap_cbf, n_cbf)) != EBIC_OK) return st;
+    if ((st = grow_pinned(ctx, ctx->h_res, ctx->hcap_res, n_res)) != EBIC_OK) return st;
+    const int64_t mask_words = params->want_masks ? (int64_t)P * 2 * ctx->W : 0;
+    if (mask_words && (st = grow(ctx, ctx->d_masks, ctx->cap_masks, mask_words, false)) != EBIC_OK)
+        return st;
+    bool use_index = false;
+    if ((st = choose_path(ctx, params, P, &use_index)) != EBIC_OK) return st;
+
+    hipStream_t s = ctx->stream;
+    std::memcpy(ctx->h_cbf, offsets, sizeof(int32_t) * ((size_t)P + 1));
+    std::memcpy(ctx->h_cbf + P + 1, cols, sizeof(int32_t) * (size_t)n_entries);
+    HIP_TRY(ctx, hipMemcpyAsync(ctx->d_cbf, ctx->h_cbf, sizeof(int32_t) * (size_t)n_cbf,
+                                hipMemcpyHostToDevice, s));
+    int32_t *d_counts = reinterpret_cast<int32_t *>(ctx->d_res + P);
+    EvalArgs e{ctx->d_cbf, ctx->d_cbf + P + 1, P, n_entries, params->sigma,
+               params->max_violations, params->negative_trends ? 1 : 0,
+               mask_words ? ctx->d_masks : nullptr, d_counts, ctx->d_res, ctx->d_log,
+               ctx->d_acc};
+    if ((st = launch_all(ctx, e, use_index, s)) != EBIC_OK) return st;
+    if (mark_repeats) HIP_TRY(ctx, launch_mark_repeats(e.offsets, e.cols, P, d_counts, s));
+    HIP_TRY(ctx, hipMemcpyAsync(ctx->h_res, ctx->d_res,
+                                sizeof(double) * (size_t)P + sizeof(int32_t) * (size_t)P,
+                                hipMemcpyDeviceToHost, s));
+    if (mask_words)
+        HIP_TRY(ctx, hipMemcpyAsync(masks, ctx->d_masks, sizeof(uint64_t) * (size_t)mask_words,
+                                    hipMemcpyDeviceToHost, s));
+    HIP_TRY(ctx, hipStreamSynchronize(s));
+    return EBIC_OK;
+}
+
+const int32_t *host_counts(const ebic_ctx *ctx, int32_t P) {
+    return reinterpret_cast<const int32_t *>(ctx->h_res + P);
+}
+}  // namespace
+}  // namespace ebic
+
 extern "C" {
 
 int64_t ebic_mask_words(int64_t n_rows) { return n_rows <= 0 ? 0 : words_of(n_rows); }
@@ -541,52 +606,25 @@ ebic_status ebic_evaluate(ebic_ctx *ctx, const int32_t *offsets, const int32_t *
     // marks repeats, and the host only looks for a mark.  (The first wrong
     // offset and the first wrong column are reported in candidate order, and
     // results with masks go straight to the caller: those calls check first.)
+    // A refusal comes before any other error of the call and leaves no index
+    // behind, as if the columns had been checked first.
     int32_t longest = 0;
     const bool offsets_ok = check_offsets(ctx, offsets, P, &longest, &st);
     const bool check_after = offsets_ok && !params->want_masks &&
                              offsets[P] >= kDeviceCheckEntries && longest <= kDeviceCheckMaxLen;
     if (!check_after && !check_cbf(ctx, offsets, cols, P, &st)) return st;
-    const int64_t n_entries = offsets[P];
-    // One upload (offsets then columns) and one download (fitness then
-    // counts), both through pinned staging buffers.
-    const int64_t n_cbf = (int64_t)P + 1 + n_entries;      // int32
-    const int64_t n_res = (int64_t)P + ((int64_t)P + 1) / 2;  // doubles: P fitness + P int32
-    HIP_TRY(ctx, hipSetDevice(ctx->device));
-    if ((st = ensure_scratch(ctx, P)) != EBIC_OK) return st;
-    if ((st = grow(ctx, ctx->d_cbf, ctx->cap_cbf, n_cbf, false)) != EBIC_OK) return st;
-    if ((st = grow(ctx, ctx->d_res, ctx->cap_res, n_res, false)) != EBIC_OK) return st;
-    if ((st = grow_pinned(ctx, ctx->h_cbf, ctx->hcap_cbf, n_cbf)) != EBIC_OK) return st;
-    if ((st = grow_pinned(ctx, ctx->h_res, ctx->hcap_res, n_res)) != EBIC_OK) return st;
-    const int64_t mask_words = params->want_masks ? (int64_t)P * 2 * ctx->W : 0;
-    if (mask_words && (st = grow(ctx, ctx->d_masks, ctx->cap_masks, mask_words, false)) != EBIC_OK)
-        return st;
-    bool use_index = false;
-    if ((st = choose_path(ctx, params, P, &use_index)) != EBIC_OK) return st;
-
-    hipStream_t s = ctx->stream;
-    std::memcpy(ctx->h_cbf, offsets, sizeof(int32_t) * ((size_t)P + 1));
-    std::memcpy(ctx->h_cbf + P + 1, cols, sizeof(int32_t) * (size_t)n_entries);
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->d_cbf, ctx->h_cbf, sizeof(int32_t) * (size_t)n_cbf,
-                                hipMemcpyHostToDevice, s));
-    int32_t *d_counts = reinterpret_cast<int32_t *>(ctx->d_res + P);
-    EvalArgs e{ctx->d_cbf, ctx->d_cbf + P + 1, P, n_entries, params->sigma,
-               params->max_violations, params->negative_trends ? 1 : 0,
-               mask_words ? ctx->d_masks : nullptr, d_counts, ctx->d_res, ctx->d_log,
-               ctx->d_acc};
-    if ((st = launch_all(ctx, e, use_index, s)) != EBIC_OK) return st;
-    if (check_after) HIP_TRY(ctx, launch_mark_repeats(e.offsets, e.cols, P, d_counts, s));
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->h_res, ctx->d_res,
-                                sizeof(double) * (size_t)P + sizeof(int32_t) * (size_t)P,
-                                hipMemcpyDeviceToHost, s));
-    if (mask_words)
-        HIP_TRY(ctx, hipMemcpyAsync(masks, ctx->d_masks, sizeof(uint64_t) * (size_t)mask_words,
-                                    hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipStreamSynchronize(s));
-    const int32_t *h_counts = reinterpret_cast<const int32_t *>(ctx->h_res + P);
-    if (check_after && any_negative(h_counts, P) && !check_cbf(ctx, offsets, cols, P, &st))
-        return st;
+    const bool had_index = ctx->idx_built;
+    st = evaluate_host(ctx, offsets, cols, P, params, masks, check_after);
+    if (check_after && (st != EBIC_OK || any_negative(host_counts(ctx, P), P))) {
+        ebic_status refusal = EBIC_OK;
+        if (!check_cbf(ctx, offsets, cols, P, &refusal)) {
+            if (!had_index) drop_index(ctx);
+            return refusal;
+        }
+    }
+    if (st != EBIC_OK) return st;
     std::memcpy(fitness, ctx->h_res, sizeof(double) * (size_t)P);
-    std::memcpy(counts, h_counts, sizeof(int32_t) * (size_t)P);
+    std::memcpy(counts, host_counts(ctx, P), sizeof(int32_t) * (size_t)P);
     return EBIC_OK;
 }
 
