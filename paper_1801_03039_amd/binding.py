@@ -1097,15 +1097,19 @@ def mask_rows(masks, n_rows: int, capacity: Optional[int] = None, stream=None):
         stream = _t.cuda.current_stream(dev)
     offsets = _t.empty(K + 1, dtype=_t.int64, device=dev)
     # Without a capacity the lists are written at once into room for
-    # _ROWS_GUESS entries (or every row of every bicluster, if that is less);
-    # only longer ones are written in a second call of their exact size.
-    cap = min(K * int(n_rows), _ROWS_GUESS) if capacity is None else int(capacity)
+    # _ROWS_GUESS entries (or every row of every bicluster, if that is less)
+    # and copied into their exact size; longer ones, and those of another
+    # stream than torch's current one, are written in a second call.
+    own = stream == _t.cuda.current_stream(dev)
+    if capacity is not None:
+        cap = int(capacity)
+    else:
+        cap = min(K * int(n_rows), _ROWS_GUESS) if own else 0
     rows = _t.empty(max(cap, 1), dtype=_t.int32, device=dev)
     args = [_vp(masks.data_ptr()), K, planes, int(n_rows), _vp(offsets.data_ptr()),
             _vp(rows.data_ptr()), cap, _vp(stream.cuda_stream)]
     _check(_mask_rows(*args))
     if capacity is None:
-        own = stream == _t.cuda.current_stream(dev)
         if not own:
             stream.synchronize()
         total = int(offsets[-1].item())
@@ -1113,8 +1117,8 @@ def mask_rows(masks, n_rows: int, capacity: Optional[int] = None, stream=None):
             rows = _t.empty(total, dtype=_t.int32, device=dev)
             args[5], args[6] = _vp(rows.data_ptr()), total
             _check(_mask_rows(*args))
-        elif total < cap // 4 and own:   # leave no large buffer behind a short list
-            rows = rows[:total].clone()
+        elif total < cap:   # leave no larger buffer behind the lists
+            rows = rows[:max(total, 1)].clone()
         cap = total
     return offsets, rows[:cap]
 
