@@ -462,8 +462,9 @@ ebic_status ebic_batch_evaluate(ebic_batch *b, const int32_t *const *offsets,
  * picks the hardware concurrency.  The launch shape is tuned on the first
  * generation unless set before. */
 /* Device time (ms) of the last batched launch: the kernel, from events on
- * the batch's stream around its launch (the run table is copied before;
- * a refused population leaves the value of the launch before). */
+ * the batch's stream around its launch (the run table is copied before it,
+ * repeated columns of large populations are looked for after it; a refused
+ * population leaves the value of the launch before). */
 double ebic_batch_last_ms(const ebic_batch *b);
 /* Device time (ms) spent building the runs' pairwise order indexes at
  * ebic_batch_create (sum over runs, from events around each build). */

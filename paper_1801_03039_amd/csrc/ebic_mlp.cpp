@@ -354,7 +354,9 @@ ebic_status upload(ebic_mlp *m, const int32_t *off, const int32_t *cols, int32_t
     ebic_status st = reserve(m, B, occurrences ? L : 0);
     if (st != EBIC_OK) return st;
     const int64_t n = (int64_t)B + 1 + L + (target ? B : 0);
-    if (m->copying) {   // the staging buffer's last copy (long done: kernels follow it)
+    // the staging buffer's last copy (behind the steps that training calls
+    // without a loss have left queued, if there are any)
+    if (m->copying) {
         MHIP(hipEventSynchronize(m->copied));
         m->copying = false;
     }

@@ -59,8 +59,9 @@ struct SplitMix64 {
     uint32_t below(const struct Modulus &n);
 };
 
-// x % n by a product: floor(x m / 2^64) with m = floor((2^64 - 1) / n) is the
-// quotient or one less, as m > 2^64 / n - 1 - 1 / n and x < 2^64.
+// x % n by a product: with m = floor((2^64 - 1) / n), which is at least
+// 2^64 / n - 1, x m / 2^64 >= x / n - x / 2^64 > x / n - 1 for x < 2^64, so its
+// floor is the quotient or one less.
 struct Modulus {
     uint64_t n, m;
     explicit Modulus(uint64_t n_ = 1) : n(n_), m(~0ull / n_) {}
