@@ -424,16 +424,18 @@ __device__ __forceinline__ void index_tile(const IndexRun &R, uint32_t tile, uin
             }
         }
     };
-    // Several entries per lane at a time (a workgroup of few lanes and many
-    // series has many), fewer where ties are looked up, for the registers.
+    // Most workgroups have an entry per lane at most.  Those of few lanes and
+    // many series stage several per lane at a time (fewer where ties are looked
+    // up, for the registers), out of the others' way.
     auto stage_span = [&](auto look_up_ties) {
         constexpr int N = decltype(look_up_ties)::value ? 2 : 4;
-        for (int32_t e = tid; (e & ~63) < span; e += N * (int32_t)blockDim.x) {
-            if ((e & ~63) + (int32_t)blockDim.x < span)
-                stage_entries(std::integral_constant<int, N>{}, look_up_ties, e);
-            else
-                stage_entries(std::integral_constant<int, 1>{}, look_up_ties, e);
+        if (__builtin_expect(span <= (int32_t)blockDim.x, 1)) {
+            if ((tid & ~63) < span)
+                stage_entries(std::integral_constant<int, 1>{}, look_up_ties, tid);
+            return;
         }
+        for (int32_t e = tid; (e & ~63) < span; e += N * (int32_t)blockDim.x)
+            stage_entries(std::integral_constant<int, N>{}, look_up_ties, e);
     };
     if (NEG && ties)
         stage_span(std::integral_constant<bool, NEG>{});
