@@ -1093,14 +1093,15 @@ def mask_rows(masks, n_rows: int, capacity: Optional[int] = None, stream=None):
         raise ValueError("masks must be a contiguous device tensor")
     K, planes = _mask_shape(masks, n_rows)
     dev = masks.device
-    if stream is None:
-        stream = _t.cuda.current_stream(dev)
+    current = _t.cuda.current_stream(dev)
+    own = stream is None or stream == current
+    if own:
+        stream = current
     offsets = _t.empty(K + 1, dtype=_t.int64, device=dev)
     # Without a capacity the lists are written at once into room for
     # _ROWS_GUESS entries (or every row of every bicluster, if that is less)
     # and copied into their exact size; longer ones, and those of another
     # stream than torch's current one, are written in a second call.
-    own = stream == _t.cuda.current_stream(dev)
     if capacity is not None:
         cap = int(capacity)
     else:
@@ -1120,7 +1121,7 @@ def mask_rows(masks, n_rows: int, capacity: Optional[int] = None, stream=None):
         elif total < cap:   # leave no larger buffer behind the lists
             rows = rows[:max(total, 1)].clone()
         cap = total
-    return offsets, rows[:cap]
+    return offsets, rows if rows.numel() == cap else rows[:cap]
 
 
 def _set_c(s, n_rows, keep):
