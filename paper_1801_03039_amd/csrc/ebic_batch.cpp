@@ -166,7 +166,8 @@ size_t run_table_bytes(int32_t n_runs) {
 }
 
 // Whether run r of request q is evaluated by the batched index kernel (else
-// by the direct kernel after it).
+// by the direct kernel after it: the batched kernel is not built for the
+// counters of tolerances above kIndexMaxViolations).
 bool via_index(const ebic_batch *b, const Request &q, int32_t r) {
     return !b->direct[(size_t)r] && q.params->max_violations <= kIndexMaxViolations;
 }
@@ -184,7 +185,7 @@ struct Cut {
 // candidates hold as many as 256 lanes do.  With 8 words per lane they hold no
 // more than the staging area takes, as the loop that reads its columns from
 // memory then has one pair in flight: 64 runs of 300-500 rows, 1024 series of
-// 10-40 columns, k = 1, both directions, take 18.9 us with half the lanes idle
+// 10-40 columns, k = 1, both directions, take 18.8 us with half the lanes idle
 // and 20.0 with all of them and columns from memory; with fewer words the idle
 // lanes cost more (1 word, 40-64 rows: 16.0 and 13.5 us).
 Cut cut_run(const int32_t *off, int32_t P, int64_t items, int32_t words, int32_t whole,

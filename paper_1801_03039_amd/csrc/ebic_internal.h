@@ -97,7 +97,7 @@ struct IndexRun {
 // and a bit each): kStageMin serves most shapes and leaves the kernels their
 // resident waves (16.3 of 160 KiB); workgroups of many or long series get up
 // to kStageMax, and past that read the columns from memory.  4096 series of
-// 50-62 columns on 320 rows, rising, k = 0, take 5.0 us with an area of
+// 50-62 columns on 320 rows, rising, k = 0, take 4.6 us with an area of
 // kStageMax; with kStageMin, and columns read from memory one pair at a time,
 // 9.4.
 constexpr int32_t kStageMin = 2048, kStageMax = 4096;
