@@ -99,9 +99,10 @@ void launch_aligned(const IndexRun &R, const EvalArgs &e, hipStream_t stream) {
     // Few lanes and many series: further waves, which only stage, until a lane
     // has about 4 entries (4096 series of 20-28 columns on 60 rows, both
     // directions, k = 1: 9.0 us with the 64 lanes of the series, 5.1 with 256).
-    const int64_t stagers = std::min<int64_t>(cpw * (e.n_entries / R.P + 1) / 4, kBlock);
-    const int64_t threads = (std::max(cpw * Wg, stagers) + kWave - 1) / kWave * kWave;
     const dim3 grid((unsigned)((R.P + cpw - 1) / cpw));
+    int64_t stagers = std::min<int64_t>(cpw * (e.n_entries / R.P + 1) / 4, kBlock);
+    if ((int64_t)grid.x * kBlock > INT32_MAX) stagers = 0;   // (a launch's lanes are limited)
+    const int64_t threads = (std::max(cpw * Wg, stagers) + kWave - 1) / kWave * kWave;
     launch_index_t<K, U, V, true, TAIL>(R, (uint32_t)cpw, grid, dim3((unsigned)threads), e,
                                         stream);
 }
